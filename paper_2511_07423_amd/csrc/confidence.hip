@@ -123,63 +123,47 @@ __global__ __launch_bounds__(256) void confidence_kernel(const void* __restrict_
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same pass, keeping the k <= 8 most probable tokens of the row as well: the compressed form of a
-// distribution that is transmitted instead of the full vector (Section 4.2, "Compression before
-// transmission"), and the margin score p_top1 - p_top2 of the layer-wise early exit (Section 4.3).
-// Each WAVEFRONT keeps the 8 best (logit, id) it has seen, sorted (equal logits: lower id first), the
-// same in all its lanes.  An element is looked at more closely only if it is not below the list's last
-// entry: a ballot finds such lanes, their values are broadcast one by one and inserted.  Over a row a
-// wavefront meets about 8 ln(n / 8) such elements, so the common path costs one compare and one ballot
-// per element.  (Per-thread lists cost ten times more: with 64 lanes in lockstep nearly every 16-byte
-// chunk has some lane that must insert.)  After the row the four lists are merged by one thread.
-#define TOPK_MAX 8
+// The same pass, keeping the k <= 256 most probable tokens of the row as well: the compressed form of a distribution
+// that is transmitted instead of the full vector (Section 4.2, "Compression before transmission": a list that cuts
+// 32000 entries by over 99.5 % has up to 160), and the margin score p_top1 - p_top2 of the layer-wise early exit
+// (Section 4.3).  Equal logits: the lower id first.
+//
+// One block of 512 threads per row (four fit a compute unit: a few hundred rows run in one round); no list is kept
+// while the row streams by.  Each thread remembers the maximum of each of its (up to NV) groups of 16-byte loads.
+// Afterwards the k-th largest of the 512 thread maxima is a lower bound of the k-th largest logit, and a tight one:
+// of independent logits about 1.4 k at k = 256, k + few for small k, are not below it.  Only the groups whose maximum reaches the bound are read again (from L2), their
+// entries that reach it are collected in LDS, and each finds its rank by comparing with all others: ranks below k
+// are the answer, in order.  Rows that put more than TOPK_CAP entries at or above the bound (plateaus of ties, masked
+// vocabularies) take an exact radix search over (logit, id) instead, which ends with k entries.
+// Bound by the one read of the row: 532 x 32000 f32, k = 160: 439 us with sorted lists kept across the lanes of
+// each wavefront (an insertion per new entry), 26 us.
+#define TOPK_WIDE_MAX 256
+#define TOPK_THREADS 512
+#define TOPK_CAP 1024
 
-struct TopEntry {
-  float v;
-  int id;
-};
-__device__ __forceinline__ bool top_before(float va, int ia, float vb, int ib) { return va > vb || (va == vb && ia < ib); }
+// Unsigned keys in the order of the logits; order_key's inverse is key_value.
+__device__ __forceinline__ uint32_t order_key(float v) {
+  const uint32_t u = __float_as_uint(v);
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+__device__ __forceinline__ float key_value(uint32_t key) {
+  return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key);
+}
+// For the lists: 0 for NaN (never listed), -0 and +0 the same.
+__device__ __forceinline__ uint32_t list_key(float v) { return v != v ? 0u : order_key(v + 0.0f); }
 
 template <bool BF16>
-__global__ __launch_bounds__(256) void confidence_topk_kernel(const void* __restrict__ logits, int64_t vocab,
-                                                              int64_t stride, int k, int32_t* __restrict__ ids,
-                                                              float* __restrict__ probs, float* __restrict__ margin,
-                                                              float* __restrict__ H) {
-  constexpr int VEC = BF16 ? 8 : 4;
-  const int64_t row = blockIdx.x;
-  const char* base = reinterpret_cast<const char*>(logits) + row * stride * (BF16 ? 2 : 4);
-  const uint4* src = reinterpret_cast<const uint4*>(base);
-  const int n_vec = (int)(vocab / VEC);
-  ConfState st = {-1e30f, 0.f, 0.f, 0};
-  float tv[TOPK_MAX];                                // wavefront-uniform
-  int ti[TOPK_MAX];
-#pragma unroll
-  for (int i = 0; i < TOPK_MAX; ++i) {
-    tv[i] = -INFINITY;
-    ti[i] = 0x7FFFFFFF;
+struct RowReader {                                   // a row as 16-byte pieces plus a ragged tail
+  static constexpr int VEC = BF16 ? 8 : 4;
+  const char* base;
+  int n_vec, n_tail;
+  __device__ __forceinline__ RowReader(const void* logits, int64_t row, int64_t vocab, int64_t stride) {
+    base = reinterpret_cast<const char*>(logits) + row * stride * (BF16 ? 2 : 4);
+    n_vec = (int)(vocab / VEC);
+    n_tail = (int)(vocab - (int64_t)n_vec * VEC);
   }
-  // v, id: this lane's element; lanes whose element is not below the list's last entry get a closer look
-  auto offer = [&](float v, int id) {
-    unsigned long long mask = __builtin_amdgcn_ballot_w64(v >= tv[TOPK_MAX - 1]);
-    while (mask) {                                   // wavefront-uniform loop
-      const int l = __builtin_ctzll(mask);
-      mask &= mask - 1;
-      const float cv = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), l));
-      const int ci = __builtin_amdgcn_readlane(id, l);
-      if (!top_before(cv, ci, tv[TOPK_MAX - 1], ti[TOPK_MAX - 1])) continue;
-      tv[TOPK_MAX - 1] = cv;
-      ti[TOPK_MAX - 1] = ci;
-#pragma unroll
-      for (int i = TOPK_MAX - 1; i > 0; --i) {
-        if (top_before(tv[i], ti[i], tv[i - 1], ti[i - 1])) {
-          const float fv = tv[i]; tv[i] = tv[i - 1]; tv[i - 1] = fv;
-          const int fi = ti[i]; ti[i] = ti[i - 1]; ti[i - 1] = fi;
-        }
-      }
-    }
-  };
-  auto consume = [&](const uint4& raw, int c) {
-    float v[VEC];
+  __device__ __forceinline__ uint4 raw(int c) const { return reinterpret_cast<const uint4*>(base)[c]; }
+  static __device__ __forceinline__ void unpack(const uint4& raw, float (&v)[VEC]) {
     if constexpr (BF16) {
       v[0] = bf2f(raw.x & 0xFFFF); v[1] = bf2f(raw.x >> 16);
       v[2] = bf2f(raw.y & 0xFFFF); v[3] = bf2f(raw.y >> 16);
@@ -189,34 +173,16 @@ __global__ __launch_bounds__(256) void confidence_topk_kernel(const void* __rest
       v[0] = __uint_as_float(raw.x); v[1] = __uint_as_float(raw.y);
       v[2] = __uint_as_float(raw.z); v[3] = __uint_as_float(raw.w);
     }
-    float cmax = v[0];
-#pragma unroll
-    for (int i = 1; i < VEC; ++i) cmax = fmaxf(cmax, v[i]);
-    if (__builtin_amdgcn_ballot_w64(cmax >= tv[TOPK_MAX - 1]) != 0) {   // some lane of the wavefront has a candidate
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) offer(v[i], c * VEC + i);
-    }
-    conf_chunk<VEC>(st, v, c * VEC);
-  };
-  // One 16-byte chunk per lane and round, all lanes of a wavefront in the same round: the lanes that hold
-  // data must meet in the same ballot (an unrolled loop whose last trip only some lanes take would split
-  // them).  In the last round the lanes past the end of the row just sit out; lane 0 of a wavefront is
-  // active whenever any of its lanes is, and its list is the one used.
-  for (int c = threadIdx.x; c < n_vec; c += 256) consume(src[c], c);
-  {
-    const int64_t tail0 = (int64_t)n_vec * VEC;
-    const int n_tail = (int)(vocab - tail0);         // < VEC
-    if (n_tail > 0) {                                // block-uniform
-      const int e = threadIdx.x;
-      float v[1] = {-INFINITY};
-      if (e < n_tail)
-        v[0] = BF16 ? bf2f(reinterpret_cast<const bf16_t*>(base)[tail0 + e]) : reinterpret_cast<const float*>(base)[tail0 + e];
-      offer(e < n_tail ? v[0] : -INFINITY, e < n_tail ? (int)(tail0 + e) : 0x7FFFFFFF);
-      if (e < n_tail) conf_chunk<1>(st, v, (int)(tail0 + e));
-    }
   }
+  __device__ __forceinline__ float tail(int e) const {
+    const int64_t at = (int64_t)n_vec * VEC + e;
+    return BF16 ? bf2f(reinterpret_cast<const bf16_t*>(base)[at]) : reinterpret_cast<const float*>(base)[at];
+  }
+};
 
-  // row statistics (m, Z, S)
+// The row's statistics from every thread's own, left in *all (LDS); ends with a barrier.
+template <int THREADS>
+__device__ __forceinline__ void conf_block_merge(ConfState st, ConfState (&red)[THREADS / 64], ConfState* all) {
   for (int o = 1; o < 64; o <<= 1) {
     ConfState other;
     other.m = __shfl_xor(st.m, o);
@@ -225,248 +191,255 @@ __global__ __launch_bounds__(256) void confidence_topk_kernel(const void* __rest
     other.id = __shfl_xor(st.id, o);
     conf_merge(st, other);
   }
-  __shared__ ConfState red[4];
-  __shared__ TopEntry cand[4][TOPK_MAX];
-  if ((threadIdx.x & 63) == 0) {
-    red[threadIdx.x >> 6] = st;
-#pragma unroll
-    for (int i = 0; i < TOPK_MAX; ++i) cand[threadIdx.x >> 6][i] = TopEntry{tv[i], ti[i]};
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = st;
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    ConfState a = red[threadIdx.x % (THREADS / 64)];
+    for (int o = 1; o < THREADS / 64; o <<= 1) {
+      ConfState other;
+      other.m = __shfl_xor(a.m, o);
+      other.Z = __shfl_xor(a.Z, o);
+      other.S = __shfl_xor(a.S, o);
+      other.id = __shfl_xor(a.id, o);
+      conf_merge(a, other);
+    }
+    if (threadIdx.x == 0) *all = a;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    ConfState a = red[0];
-    conf_merge(a, red[1]);
-    conf_merge(a, red[2]);
-    conf_merge(a, red[3]);
-    if (H) H[row] = logf(a.Z) - a.S / a.Z;
-    // merge the four sorted lists: k rounds of "best head"
-    int head[4] = {0, 0, 0, 0};
-    float p_first = 0.f, p_second = 0.f;
-    const int rounds = k > 2 ? k : 2;                // the margin needs the two best whatever k is
-    for (int r = 0; r < rounds; ++r) {
-      int best = -1;
-      for (int w = 0; w < 4; ++w) {
-        if (head[w] >= TOPK_MAX) continue;
-        const TopEntry e = cand[w][head[w]];
-        if (best < 0 || top_before(e.v, e.id, cand[best][head[best]].v, cand[best][head[best]].id)) best = w;
-      }
-      const TopEntry wn = best >= 0 ? cand[best][head[best]] : TopEntry{-INFINITY, 0x7FFFFFFF};
-      if (best >= 0) ++head[best];
-      const bool have = wn.id != 0x7FFFFFFF;         // false only for a row with fewer than r+1 comparable entries
-      const float pr = have ? fast_exp2((wn.v - a.m) * LOG2E) / a.Z : 0.f;
-      if (r < k) {
-        ids[row * k + r] = have ? wn.id : 0;
-        probs[row * k + r] = pr;
-      }
-      if (r == 0) p_first = pr;
-      if (r == 1) p_second = pr;
-    }
-    if (margin) margin[row] = p_first - p_second;
-  }
 }
 
-// ---------------------------------------------------------------------------------------------
-// The same for 8 < k <= 256, the size of a transmitted list ("Compression before transmission" cuts 32000
-// entries by over 99.5 %: up to 160).  Two levels.  Level 1: each wavefront keeps its k best (logit, id) sorted
-// across its LANES -- entry p lives in register p / 64 of lane p % 64 -- so an insertion is a handful of
-// wavefront-wide instructions whatever k is: a ballot counts the entries that come before the candidate, every
-// lane at or behind that position takes its left neighbour's entry (the entry of lane 63 crosses into lane 0 of
-// the next register), and the lane at the position takes the candidate.  Candidates are found as above (a
-// ballot against the list's k-th entry).  Level 2: the four sorted lists meet in LDS and every entry computes its
-// final rank as its position in its own list plus, by binary search, the number of entries of the other three
-// lists that come before it; ranks below k are the result, already in order.
-#define TOPK_WIDE_MAX 256
-
-template <bool BF16, int R>
-__global__ __launch_bounds__(256) void confidence_topk_wide_kernel(const void* __restrict__ logits, int64_t vocab,
-                                                                   int64_t stride, int k, int32_t* __restrict__ ids,
-                                                                   float* __restrict__ probs, float* __restrict__ margin,
-                                                                   float* __restrict__ H) {
-  constexpr int VEC = BF16 ? 8 : 4;
+template <bool BF16, int NV, bool MULTI>
+__global__ __launch_bounds__(TOPK_THREADS) void confidence_topk_kernel(const void* __restrict__ logits, int64_t vocab,
+                                                                       int64_t stride, int k, int32_t* __restrict__ ids,
+                                                                       float* __restrict__ probs,
+                                                                       float* __restrict__ margin, float* __restrict__ H) {
+  constexpr int VEC = RowReader<BF16>::VEC;
+  __shared__ ConfState red[TOPK_THREADS / 64], all;
+  __shared__ __attribute__((aligned(16))) unsigned long long list[TOPK_CAP];   // (key, ~id): larger comes first
+  __shared__ __attribute__((aligned(16))) uint32_t keys[TOPK_THREADS];
+  __shared__ int cnts[2][TOPK_THREADS / 64];
+  __shared__ int n_list;
+  __shared__ float p_top[2];
   const int64_t row = blockIdx.x;
-  const char* base = reinterpret_cast<const char*>(logits) + row * stride * (BF16 ? 2 : 4);
-  const uint4* src = reinterpret_cast<const uint4*>(base);
-  const int n_vec = (int)(vocab / VEC);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  ConfState st = {-1e30f, 0.f, 0.f, 0};
-  float ev[R];                                       // entry p = r * 64 + lane of the wavefront's sorted list
-  int ei[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    ev[r] = -INFINITY;
-    ei[r] = 0x7FFFFFFF;
-  }
-  float thr_v = -INFINITY;                           // the list's k-th entry (wavefront-uniform)
-  int thr_i = 0x7FFFFFFF;
-  const int kr = (k - 1) >> 6, kl = (k - 1) & 63;    // where entry k - 1 lives
+  const RowReader<BF16> rd(logits, row, vocab, stride);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int want = max(k, 2);                        // the margin needs the two best whatever k is
+  // group j of this thread: loads (j per + g) 1024 + tid, g < per
+  const int per = MULTI ? (rd.n_vec + NV * TOPK_THREADS - 1) / (NV * TOPK_THREADS) : 1;
 
-  auto insert = [&](float cv, int ci) {              // wavefront-uniform candidate that comes before the k-th entry
-    int pos = 0;
+  // ---- the row streams by
+  ConfState st = {-1e30f, 0.f, 0.f, 0};
+  float gmax[NV];                                    // NaN: nothing comparable in the group
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-      pos += __builtin_popcountll(__builtin_amdgcn_ballot_w64(top_before(ev[r], ei[r], cv, ci)));
+  for (int j = 0; j < NV; ++j) gmax[j] = __uint_as_float(0x7FC00000u);
+  auto take = [&](const uint4& raw, int c, float& top) {
+    float v[VEC];
+    RowReader<BF16>::unpack(raw, v);
 #pragma unroll
-    for (int r = R - 1; r >= 0; --r) {
-      float upv = __shfl_up(ev[r], 1);
-      int upi = __shfl_up(ei[r], 1);
-      if (r > 0) {
-        const float cross_v = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ev[r - 1]), 63));
-        const int cross_i = __builtin_amdgcn_readlane(ei[r - 1], 63);
-        if (lane == 0) {
-          upv = cross_v;
-          upi = cross_i;
+    for (int i = 0; i < VEC; ++i) top = fmaxf(top, v[i]);
+    conf_chunk<VEC>(st, v, c * VEC);
+  };
+  if constexpr (MULTI) {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      int c = j * per * TOPK_THREADS + tid;
+#pragma unroll 4
+      for (int g = 0; g < per; ++g, c += TOPK_THREADS) {
+        const uint4 raw = rd.raw(min(c, rd.n_vec - 1));   // clamped, not skipped: the loads stay in flight together
+        if (c < rd.n_vec) take(raw, c, gmax[j]);
+      }
+    }
+  } else {
+    constexpr int FLY = 4;                           // loads in flight per thread
+#pragma unroll
+    for (int j0 = 0; j0 < NV; j0 += FLY) {
+      uint4 raw[FLY];
+#pragma unroll
+      for (int f = 0; f < FLY; ++f) {
+        const int c = (j0 + f) * TOPK_THREADS + tid;
+        raw[f] = c < rd.n_vec ? rd.raw(c) : make_uint4(0u, 0u, 0u, 0u);
+      }
+#pragma unroll
+      for (int f = 0; f < FLY; ++f) {
+        const int c = (j0 + f) * TOPK_THREADS + tid;
+        if (c < rd.n_vec) take(raw[f], c, gmax[j0 + f]);
+      }
+    }
+  }
+  uint32_t tail_key = 0;
+  if (tid < rd.n_tail) {
+    float v[1] = {rd.tail(tid)};
+    tail_key = list_key(v[0]);
+    conf_chunk<1>(st, v, rd.n_vec * VEC + tid);
+  }
+  float tmax = gmax[0];
+#pragma unroll
+  for (int j = 1; j < NV; ++j) tmax = fmaxf(tmax, gmax[j]);
+  keys[tid] = max(list_key(tmax), tail_key);
+  if (tid == 0) n_list = 0;
+  if (tid < 2) p_top[tid] = 0.f;
+  conf_block_merge<TOPK_THREADS>(st, red, &all);
+
+  // ---- the want-th largest thread maximum, to its upper 24 bits: each wavefront counts for one of the 8 next digits
+  uint32_t bound = 0;
+  {
+    uint4 q[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) q[i] = *reinterpret_cast<const uint4*>(keys + i * 256 + lane * 4);
+    int buf = 0;
+#pragma unroll
+    for (int shift = 29; shift >= 8; shift -= 3) {
+      const uint32_t t = bound | ((uint32_t)wave << shift);
+      int n = 0;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(q[i].x >= t)) + __builtin_popcountll(__builtin_amdgcn_ballot_w64(q[i].y >= t)) +
+             __builtin_popcountll(__builtin_amdgcn_ballot_w64(q[i].z >= t)) + __builtin_popcountll(__builtin_amdgcn_ballot_w64(q[i].w >= t));
+      if (lane == 0) cnts[buf][wave] = n;
+      __syncthreads();
+      const unsigned long long ok = __builtin_amdgcn_ballot_w64(cnts[buf][lane & 7] >= want) & 0xFFull;   // bit 0 always
+      bound |= (uint32_t)(31 - __builtin_clz((uint32_t)ok | 1u)) << shift;
+      buf ^= 1;
+    }
+  }
+  bound = max(bound, 1u);                            // fewer than want threads saw anything: every comparable entry
+
+  // ---- collect what reaches the bound
+  auto composite = [](uint32_t key, int id) { return ((unsigned long long)key << 32) | (0xFFFFFFFFu - (uint32_t)id); };
+  auto push = [&](unsigned long long c) {
+    const int at = atomicAdd(&n_list, 1);
+    if (at < TOPK_CAP) list[at] = c;
+  };
+  {
+    uint32_t hit = 0;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) hit |= list_key(gmax[j]) >= bound ? 1u << j : 0u;
+    while (hit) {                                    // lanes take their groups side by side
+      const int j = __builtin_ctz(hit);
+      hit &= hit - 1;
+      for (int g = 0; g < per; ++g) {
+        const int c = (j * per + g) * TOPK_THREADS + tid;
+        if (c >= rd.n_vec) break;
+        float v[VEC];
+        RowReader<BF16>::unpack(rd.raw(c), v);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+          const uint32_t key = list_key(v[i]);
+          if (key >= bound) push(composite(key, c * VEC + i));
         }
       }
-      const int p = r * 64 + lane;
-      ev[r] = p < pos ? ev[r] : (p == pos ? cv : upv);
-      ei[r] = p < pos ? ei[r] : (p == pos ? ci : upi);
     }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (r == kr) {
-        thr_v = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ev[r]), kl));
-        thr_i = __builtin_amdgcn_readlane(ei[r], kl);
-      }
-  };
-  auto offer = [&](float v, int id) {
-    unsigned long long mask = __builtin_amdgcn_ballot_w64(top_before(v, id, thr_v, thr_i));
-    while (mask) {                                   // wavefront-uniform loop
-      const int l = __builtin_ctzll(mask);
-      mask &= mask - 1;
-      const float cv = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), l));
-      const int ci = __builtin_amdgcn_readlane(id, l);
-      if (top_before(cv, ci, thr_v, thr_i)) insert(cv, ci);   // the k-th entry may have moved up meanwhile
-    }
-  };
-  // The list lives across the lanes, so EVERY lane of the wavefront walks through every insertion: the loop
-  // below has no divergent arm; a lane past the end of the row carries -inf entries that are never candidates.
-  auto consume = [&](const uint4& raw, int c, bool valid) {
-    float v[VEC];
-    if constexpr (BF16) {
-      v[0] = bf2f(raw.x & 0xFFFF); v[1] = bf2f(raw.x >> 16);
-      v[2] = bf2f(raw.y & 0xFFFF); v[3] = bf2f(raw.y >> 16);
-      v[4] = bf2f(raw.z & 0xFFFF); v[5] = bf2f(raw.z >> 16);
-      v[6] = bf2f(raw.w & 0xFFFF); v[7] = bf2f(raw.w >> 16);
-    } else {
-      v[0] = __uint_as_float(raw.x); v[1] = __uint_as_float(raw.y);
-      v[2] = __uint_as_float(raw.z); v[3] = __uint_as_float(raw.w);
-    }
-    float cmax = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) cmax = fmaxf(cmax, valid ? v[i] : -INFINITY);
-    if (__builtin_amdgcn_ballot_w64(cmax >= thr_v) != 0) {   // wavefront-uniform
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) offer(valid ? v[i] : -INFINITY, valid ? c * VEC + i : 0x7FFFFFFF);
-    }
-    if (valid) conf_chunk<VEC>(st, v, c * VEC);        // per-lane state: may diverge
-  };
-  const int rounds = (n_vec + 255) / 256;
-  for (int it = 0; it < rounds; ++it) {
-    const int c = it * 256 + threadIdx.x;
-    const bool valid = c < n_vec;
-    const uint4 raw = valid ? src[c] : make_uint4(0u, 0u, 0u, 0u);
-    consume(raw, c, valid);
+    if (tail_key >= bound) push(composite(tail_key, rd.n_vec * VEC + tid));
   }
-  {
-    const int64_t tail0 = (int64_t)n_vec * VEC;
-    const int n_tail = (int)(vocab - tail0);         // < VEC
-    if (n_tail > 0) {                                // block-uniform
-      const int e = threadIdx.x;
-      float v[1] = {-INFINITY};
-      if (e < n_tail)
-        v[0] = BF16 ? bf2f(reinterpret_cast<const bf16_t*>(base)[tail0 + e]) : reinterpret_cast<const float*>(base)[tail0 + e];
-      offer(e < n_tail ? v[0] : -INFINITY, e < n_tail ? (int)(tail0 + e) : 0x7FFFFFFF);
-      if (e < n_tail) conf_chunk<1>(st, v, (int)(tail0 + e));
+  __syncthreads();
+  int n = n_list;
+  if (n > TOPK_CAP) {                                // block-uniform
+    // ---- exact search: (key, ~id) digit by digit, 8 bits per pass over the row
+    uint32_t* bins = keys;                           // 256 counters
+    __shared__ unsigned long long sh_prefix;
+    __shared__ int sh_above, sh_done;
+    if (tid == 0) {
+      sh_prefix = 0;
+      sh_above = 0;
+      sh_done = 0;
     }
+    for (int shift = 56; shift >= 0; shift -= 8) {
+      if (tid < 256) bins[tid] = 0;
+      __syncthreads();
+      if (sh_done) break;                            // block-uniform; nothing below is left out of step
+      const unsigned long long prefix = sh_prefix;
+      auto add = [&](float v, int id, bool on) {
+        const uint32_t key = list_key(v);
+        const unsigned long long c = composite(key, id);
+        on = on && key != 0 && (shift == 56 || (c >> ((shift + 8) & 63)) == (prefix >> ((shift + 8) & 63)));
+        const uint32_t bin = (uint32_t)(c >> shift) & 255u;
+        // ties are why a row is here: the lanes that share the first lane's bin count as one
+        const unsigned long long act = __builtin_amdgcn_ballot_w64(on);
+        if (!act) return;
+        const int l0 = __builtin_ctzll(act);
+        const uint32_t b0 = __builtin_amdgcn_readlane(bin, l0);
+        const unsigned long long same = __builtin_amdgcn_ballot_w64(on && bin == b0);
+        if (lane == l0) atomicAdd(&bins[b0], (uint32_t)__builtin_popcountll(same));
+        if (on && bin != b0) atomicAdd(&bins[bin], 1u);
+      };
+      for (int c0 = 0; c0 < rd.n_vec; c0 += TOPK_THREADS) {   // uniform trip count: whole wavefronts in `add`
+        const int c = c0 + tid;
+        float v[VEC];
+        RowReader<BF16>::unpack(rd.raw(min(c, rd.n_vec - 1)), v);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) add(v[i], c * VEC + i, c < rd.n_vec);
+      }
+      if (rd.n_tail > 0) add(tid < rd.n_tail ? rd.tail(tid) : 0.f, rd.n_vec * VEC + tid, tid < rd.n_tail);
+      __syncthreads();
+      if (tid == 0) {
+        int above = sh_above, b = 255;
+        for (; b > 0 && above + (int)bins[b] < want; --b) above += (int)bins[b];
+        sh_prefix = prefix | ((unsigned long long)b << shift);
+        sh_above = above;
+        if (above + (int)bins[b] <= want) sh_done = 1;  // the whole bin belongs to the list
+        n_list = 0;
+      }
+      __syncthreads();
+    }
+    const unsigned long long least = sh_prefix;
+    auto keep = [&](float v, int id) {
+      const uint32_t key = list_key(v);
+      const unsigned long long c = composite(key, id);
+      if (key != 0 && c >= least) push(c);
+    };
+    for (int c = tid; c < rd.n_vec; c += TOPK_THREADS) {
+      float v[VEC];
+      RowReader<BF16>::unpack(rd.raw(c), v);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) keep(v[i], c * VEC + i);
+    }
+    if (tid < rd.n_tail) keep(rd.tail(tid), rd.n_vec * VEC + tid);
+    __syncthreads();
+    n = n_list;
   }
 
-  for (int o = 1; o < 64; o <<= 1) {
-    ConfState other;
-    other.m = __shfl_xor(st.m, o);
-    other.Z = __shfl_xor(st.Z, o);
-    other.S = __shfl_xor(st.S, o);
-    other.id = __shfl_xor(st.id, o);
-    conf_merge(st, other);
+  // ---- ranks
+  const float m = all.m, inv_z = 1.0f / all.Z;
+  for (int at = tid; at < n; at += TOPK_THREADS) {
+    const unsigned long long mine = list[at];
+    int rank = 0, e = 0;
+    for (; e + 1 < n; e += 2) {
+      const ulonglong2 two = *reinterpret_cast<const ulonglong2*>(list + e);
+      rank += (two.x > mine) + (two.y > mine);
+    }
+    if (e < n) rank += list[e] > mine;
+    const float pr = fast_exp2((key_value((uint32_t)(mine >> 32)) - m) * LOG2E) * inv_z;
+    if (rank < k) {
+      ids[row * k + rank] = (int32_t)(0xFFFFFFFFu - (uint32_t)mine);
+      probs[row * k + rank] = pr;
+    }
+    if (rank < 2) p_top[rank] = pr;
   }
-  __shared__ ConfState red[4];
-  __shared__ float cv_[4][TOPK_WIDE_MAX];
-  __shared__ int ci_[4][TOPK_WIDE_MAX];
-  __shared__ int n_valid[4];
-  __shared__ float sh_m, sh_z;
-  if (lane == 0) red[wave] = st;
-  int mine = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    cv_[wave][r * 64 + lane] = ev[r];
-    ci_[wave][r * 64 + lane] = ei[r];
-    mine += __builtin_popcountll(__builtin_amdgcn_ballot_w64(ei[r] != 0x7FFFFFFF && r * 64 + lane < k));
-  }
-  if (lane == 0) n_valid[wave] = mine;
-  // defaults for a row with fewer than k comparable entries
-  for (int e = threadIdx.x; e < k; e += 256) {
+  for (int e = n + tid; e < k; e += TOPK_THREADS) {  // a row with fewer than k comparable entries
     ids[row * k + e] = 0;
     probs[row * k + e] = 0.f;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    ConfState a = red[0];
-    conf_merge(a, red[1]);
-    conf_merge(a, red[2]);
-    conf_merge(a, red[3]);
-    if (H) H[row] = logf(a.Z) - a.S / a.Z;
-    sh_m = a.m;
-    sh_z = a.Z;
+  if (tid == 0) {
+    if (H) H[row] = logf(all.Z) - all.S / all.Z;
+    if (margin) margin[row] = p_top[0] - p_top[1];
   }
-  __syncthreads();
-  const float m = sh_m, Z = sh_z;
-  __shared__ float p_top[2];
-  if (threadIdx.x < 2) p_top[threadIdx.x] = 0.f;
-  __syncthreads();
-  for (int w = 0; w < 4; ++w) {
-    const int e = threadIdx.x;                       // entry e of list w
-    if (e >= n_valid[w]) continue;
-    const float v = cv_[w][e];
-    const int id = ci_[w][e];
-    int rank = e;
-    for (int o = 0; o < 4; ++o) {
-      if (o == w) continue;
-      int lo = 0, hi = n_valid[o];                   // first entry of list o that does not come before (v, id)
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (top_before(cv_[o][mid], ci_[o][mid], v, id)) lo = mid + 1; else hi = mid;
-      }
-      rank += lo;
-    }
-    if (rank < k) {
-      const float pr = fast_exp2((v - m) * LOG2E) / Z;
-      ids[row * k + rank] = id;
-      probs[row * k + rank] = pr;
-      if (rank < 2) p_top[rank] = pr;
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0 && margin) margin[row] = p_top[0] - p_top[1];
 }
 
 hipError_t launch_confidence_topk(const void* logits, int dtype, int64_t rows, int64_t vocab, int64_t stride, int k,
                                   int32_t* ids, float* probs, float* margin, float* H, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  const unsigned grid = (unsigned)rows;
-  if (k <= TOPK_MAX) {
-    if (dtype == 1)
-      confidence_topk_kernel<true><<<grid, 256, 0, s>>>(logits, vocab, stride, k, ids, probs, margin, H);
-    else
-      confidence_topk_kernel<false><<<grid, 256, 0, s>>>(logits, vocab, stride, k, ids, probs, margin, H);
-    return hipGetLastError();
-  }
   if (k > TOPK_WIDE_MAX) return hipErrorInvalidValue;
-#define SY_WIDE(R_)                                                                                              \
-  if (dtype == 1)                                                                                                \
-    confidence_topk_wide_kernel<true, R_><<<grid, 256, 0, s>>>(logits, vocab, stride, k, ids, probs, margin, H); \
-  else                                                                                                           \
-    confidence_topk_wide_kernel<false, R_><<<grid, 256, 0, s>>>(logits, vocab, stride, k, ids, probs, margin, H);
-  if (k <= 64) { SY_WIDE(1) } else if (k <= 128) { SY_WIDE(2) } else if (k <= 192) { SY_WIDE(3) } else { SY_WIDE(4) }
-#undef SY_WIDE
+  const unsigned grid = (unsigned)rows;
+  const int64_t loads = (vocab / (dtype == 1 ? 8 : 4) + TOPK_THREADS - 1) / TOPK_THREADS;   // per thread
+  // as many remembered maxima as a thread has loads, up to 32; then groups of loads share one
+#define SY_TOPK(NV_, MULTI_)                                                                                          \
+  if (dtype == 1)                                                                                                     \
+    confidence_topk_kernel<true, NV_, MULTI_><<<grid, TOPK_THREADS, 0, s>>>(logits, vocab, stride, k, ids, probs, margin, H); \
+  else                                                                                                                \
+    confidence_topk_kernel<false, NV_, MULTI_><<<grid, TOPK_THREADS, 0, s>>>(logits, vocab, stride, k, ids, probs, margin, H);
+  if (loads <= 8) { SY_TOPK(8, false) } else if (loads <= 16) { SY_TOPK(16, false) } else if (loads <= 32) { SY_TOPK(32, false) } else { SY_TOPK(32, true) }
+#undef SY_TOPK
   return hipGetLastError();
 }
 
@@ -480,14 +453,6 @@ hipError_t launch_confidence_topk(const void* logits, int dtype, int64_t rows, i
 // 40-bit fixed point with integer atomics, so the sums do not depend on the order in which the threads arrive and
 // the integer result is reproducible.  After four passes the prefix is one logit value; of its holders (ties) only
 // as many as needed are counted.
-__device__ __forceinline__ uint32_t order_key(float v) {
-  const uint32_t u = __float_as_uint(v);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-__device__ __forceinline__ float key_value(uint32_t key) {
-  return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key);
-}
-
 template <bool BF16>
 __global__ __launch_bounds__(256) void nucleus_kernel(const void* __restrict__ logits, int64_t vocab, int64_t stride,
                                                       float top_p, int32_t* __restrict__ count, float* __restrict__ mass,
@@ -676,25 +641,44 @@ hipError_t launch_chunk_dispatch(const float* p1, const int32_t* cu_rows, int B,
 // Top-p (nucleus) cut of compressed distributions: row r holds k probabilities, most probable first (the
 // output of confidence_topk_kernel); n[r] = the smallest count whose float32 running sum, in list order,
 // reaches top_p (all k if it never does), mass[r] = that sum.
-__global__ void topp_count_kernel(const float* __restrict__ probs, int64_t rows, int k, float top_p,
-                                  int32_t* __restrict__ n, float* __restrict__ mass) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The running sum is serial by definition (its rounding decides the count), so the row comes in with coalesced loads,
+// one entry per lane, and the lanes' entries are added one after the other from registers: a wavefront per row
+// (a thread per row spent its time on a chain of uncoalesced loads: 532 lists of 160, 20 us, 4 us).
+__global__ __launch_bounds__(256) void topp_count_kernel(const float* __restrict__ probs, int64_t rows, int k, float top_p,
+                                                         int32_t* __restrict__ n, float* __restrict__ mass) {
+  const int64_t r = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (r >= rows) return;
+  const int lane = threadIdx.x & 63;
   float acc = 0.f;
-  int kept = 0;
-  for (int i = 0; i < k; ++i) {
-    acc += probs[r * k + i];
-    kept = i + 1;
-    if (acc >= top_p) break;
+  int kept = k;
+  float next = lane < k ? probs[r * k + lane] : 0.f;
+  for (int i0 = 0; i0 < k; i0 += 64) {
+    const float cur = next;
+    if (i0 + 64 < k) next = i0 + 64 + lane < k ? probs[r * k + i0 + 64 + lane] : 0.f;
+    float upto = 0.f;                                // lane i: the running sum after entry i0 + i
+#pragma unroll
+    for (int i = 0; i < 64; ++i) {                   // past the end: adds 0
+      acc += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(cur), i));
+      upto = lane == i ? acc : upto;
+    }
+    const unsigned long long over = __builtin_amdgcn_ballot_w64(i0 + lane < k && upto >= top_p);
+    if (over) {
+      const int i = __builtin_ctzll(over);
+      kept = i0 + i + 1;
+      acc = __shfl(upto, i);
+      break;
+    }
   }
-  n[r] = kept;
-  if (mass) mass[r] = acc;
+  if (lane == 0) {
+    n[r] = kept;
+    if (mass) mass[r] = acc;
+  }
 }
 
 hipError_t launch_topp_count(const float* probs, int64_t rows, int k, float top_p, int32_t* n, float* mass,
                              hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  topp_count_kernel<<<(unsigned)((rows + 127) / 128), 128, 0, s>>>(probs, rows, k, top_p, n, mass);
+  topp_count_kernel<<<(unsigned)((rows + 3) / 4), 256, 0, s>>>(probs, rows, k, top_p, n, mass);
   return hipGetLastError();
 }
 
