@@ -445,169 +445,296 @@ hipError_t launch_confidence_topk(const void* logits, int dtype, int64_t rows, i
 
 // ---------------------------------------------------------------------------------------------
 // Full-vocabulary top-p (nucleus): per row the smallest number of tokens, most probable first (equal logits by
-// the lower id), whose probabilities sum to top_p, their mass, and the smallest logit kept.  One block per row.
-// After the statistics pass (m, Z) the cut is found by a radix search over the 32-bit order-preserving key of the
-// logits, 8 bits per pass from the top: every pass re-reads the row (from L2), adds each element whose key
-// matches the prefix found so far to one of 256 bins -- its count and its probability mass -- and the bin in which
-// the running mass, taken from the largest keys down, reaches top_p extends the prefix.  Masses are summed as
-// 40-bit fixed point with integer atomics, so the sums do not depend on the order in which the threads arrive and
-// the integer result is reproducible.  After four passes the prefix is one logit value; of its holders (ties) only
-// as many as needed are counted.
+// the lower id), whose probabilities sum to top_p, their mass, and the smallest logit kept.
+//
+// One block of 512 threads per row, four on a compute unit.  After the statistics pass (m, Z) the row is read twice
+// more, from L2 or the last-level cache (kept in registers instead, half as many rows fit a compute unit: 50 against
+// 46 us on 532 rows, 480 against 300 us on 2048 x 128256 bf16).  The cut is found by histogram: 1024 bins of 1/32 in the
+// logit below the maximum, each with its entries' count and probability mass (one packed LDS atomic per entry; the bins are
+// narrow so that the lanes of a wavefront rarely meet in one).  The bin where the running mass, from the largest
+// logits down, reaches top_p holds a few dozen entries: they are listed and each sums the masses above itself.  A bin
+// with more than NUC_CAP entries is first cut again by the order-preserving integer keys of its logits, down to a
+// single key if need be (ties).  Masses are 40-bit fixed point: integer sums do not depend on the order in which
+// threads arrive, so the result is reproducible.
+// Bound by the one read of the row and, for few rows, by the chain of barriers: 532 x 32000 f32: 176 us with a
+// four-pass radix search over the keys (every entry through two 64-bit LDS atomics on at most a handful of bins),
+// 46 us.
+#define NUC_THREADS 512
+#define NUC_STAT_THREADS 256
+#define NUC_BINS (2 * NUC_THREADS)
+#define NUC_CAP 512
+#define NUC_COUNT_SHIFT 42       // a bin packs (count << 42) + mass: masses of a row sum to 2^40 (1 + rounding)
+
 template <bool BF16>
-__global__ __launch_bounds__(256) void nucleus_kernel(const void* __restrict__ logits, int64_t vocab, int64_t stride,
-                                                      float top_p, int32_t* __restrict__ count, float* __restrict__ mass,
-                                                      float* __restrict__ cut_logit) {
-  constexpr int VEC = BF16 ? 8 : 4;
-  const int64_t row = blockIdx.x;
-  const char* base = reinterpret_cast<const char*>(logits) + row * stride * (BF16 ? 2 : 4);
-  const uint4* src = reinterpret_cast<const uint4*>(base);
-  const int n_vec = (int)(vocab / VEC);
-  auto load = [&](int c, float (&v)[VEC]) {
-    const uint4 raw = src[c];
-    if constexpr (BF16) {
-      v[0] = bf2f(raw.x & 0xFFFF); v[1] = bf2f(raw.x >> 16);
-      v[2] = bf2f(raw.y & 0xFFFF); v[3] = bf2f(raw.y >> 16);
-      v[4] = bf2f(raw.z & 0xFFFF); v[5] = bf2f(raw.z >> 16);
-      v[6] = bf2f(raw.w & 0xFFFF); v[7] = bf2f(raw.w >> 16);
-    } else {
-      v[0] = __uint_as_float(raw.x); v[1] = __uint_as_float(raw.y);
-      v[2] = __uint_as_float(raw.z); v[3] = __uint_as_float(raw.w);
-    }
-  };
-  auto tail_value = [&](int64_t e) {
-    return BF16 ? bf2f(reinterpret_cast<const bf16_t*>(base)[e]) : reinterpret_cast<const float*>(base)[e];
-  };
-  // ---- statistics
-  ConfState st = {-1e30f, 0.f, 0.f, 0};
-  for (int c = threadIdx.x; c < n_vec; c += 256) {
-    float v[VEC];
-    load(c, v);
-    conf_chunk<VEC>(st, v, c * VEC);
-  }
-  for (int64_t e = (int64_t)n_vec * VEC + threadIdx.x; e < vocab; e += 256) {
-    float v[1] = {tail_value(e)};
-    conf_chunk<1>(st, v, (int)e);
-  }
-  for (int o = 1; o < 64; o <<= 1) {
-    ConfState other;
-    other.m = __shfl_xor(st.m, o);
-    other.Z = __shfl_xor(st.Z, o);
-    other.S = __shfl_xor(st.S, o);
-    other.id = __shfl_xor(st.id, o);
-    conf_merge(st, other);
-  }
-  __shared__ ConfState red[4];
-  __shared__ unsigned long long bin_mass[256];
-  __shared__ unsigned int bin_count[256];
-  __shared__ uint32_t sh_prefix;
-  __shared__ unsigned long long sh_mass_above;
-  __shared__ unsigned int sh_count_above;
+__global__ __launch_bounds__(NUC_THREADS, 8) void nucleus_kernel(const void* __restrict__ logits, int64_t vocab,
+                                                              int64_t stride, float top_p, int32_t* __restrict__ count,
+                                                              float* __restrict__ mass, float* __restrict__ cut_logit) {
+  constexpr int VEC = RowReader<BF16>::VEC;
+  __shared__ ConfState red[NUC_STAT_THREADS / 64];
   __shared__ float sh_m, sh_inv_z;
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = st;
+  __shared__ __attribute__((aligned(16))) unsigned long long bins[NUC_BINS];
+  __shared__ uint32_t wide_count[NUC_BINS];          // counts of rows too long for the packed form
+  __shared__ unsigned long long l_mass[NUC_CAP];
+  __shared__ uint32_t l_key[NUC_CAP];
+  __shared__ unsigned long long w_mass[NUC_THREADS / 64];
+  __shared__ uint32_t w_count[NUC_THREADS / 64], w_last[NUC_THREADS / 64];
+  __shared__ unsigned long long sh_above, sh_bin_mass;
+  __shared__ uint32_t sh_count_above, sh_bin_count, sh_bin, sh_lo, sh_hi;
+  __shared__ int n_list;
+  const int64_t row = blockIdx.x;
+  const RowReader<BF16> rd(logits, row, vocab, stride);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool wide = vocab >= (1ll << (64 - NUC_COUNT_SHIFT));
+  auto each_value = [&](auto&& g) {                  // g(value) for every entry of the row
+#pragma unroll 4
+    for (int c = tid; c < rd.n_vec; c += NUC_THREADS) {
+      float v[VEC];
+      RowReader<BF16>::unpack(rd.raw(c), v);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) g(v[i]);
+    }
+    if (tid < rd.n_tail) g(rd.tail(tid));
+  };
+
+  // ---- statistics, by the first 256 threads: a count is an integer decided by sums over thousands of tokens, and one
+  // in a hundred of them turns on the last bit of Z, so Z is summed in one fixed order whatever the block's size
+  if (tid < NUC_STAT_THREADS) {                      // wavefront-uniform
+    ConfState st = {-1e30f, 0.f, 0.f, 0};
+    auto fold = [&](const uint4& raw, int c) {
+      float v[VEC];
+      RowReader<BF16>::unpack(raw, v);
+      conf_chunk<VEC>(st, v, c * VEC);
+    };
+    int c = tid;
+    for (; c + 3 * NUC_STAT_THREADS < rd.n_vec; c += 4 * NUC_STAT_THREADS) {   // four loads in flight per thread
+      const uint4 r0 = rd.raw(c), r1 = rd.raw(c + NUC_STAT_THREADS), r2 = rd.raw(c + 2 * NUC_STAT_THREADS), r3 = rd.raw(c + 3 * NUC_STAT_THREADS);
+      fold(r0, c);
+      fold(r1, c + NUC_STAT_THREADS);
+      fold(r2, c + 2 * NUC_STAT_THREADS);
+      fold(r3, c + 3 * NUC_STAT_THREADS);
+    }
+    for (; c < rd.n_vec; c += NUC_STAT_THREADS) fold(rd.raw(c), c);
+    if (tid < rd.n_tail) {
+      const float v[1] = {rd.tail(tid)};
+      conf_chunk<1>(st, v, rd.n_vec * VEC + tid);
+    }
+    for (int o = 1; o < 64; o <<= 1) {
+      ConfState other;
+      other.m = __shfl_xor(st.m, o);
+      other.Z = __shfl_xor(st.Z, o);
+      other.S = 0.f;
+      other.id = 0;
+      conf_merge(st, other);
+    }
+    if (lane == 0) red[wave] = st;
+  } else {
+    for (int i = tid - NUC_STAT_THREADS; i < NUC_BINS; i += NUC_THREADS - NUC_STAT_THREADS) {
+      bins[i] = 0;
+      wide_count[i] = 0;
+    }
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     ConfState a = red[0];
-    conf_merge(a, red[1]);
-    conf_merge(a, red[2]);
-    conf_merge(a, red[3]);
+#pragma unroll
+    for (int w = 1; w < NUC_STAT_THREADS / 64; ++w) conf_merge(a, red[w]);
     sh_m = a.m;
     sh_inv_z = 1.0f / a.Z;
-    sh_prefix = 0;
-    sh_mass_above = 0;
-    sh_count_above = 0;
   }
   __syncthreads();
   const float m = sh_m, inv_z = sh_inv_z;
-  const double FIX = 1099511627776.0;                // 2^40
-  auto fixed_mass = [&](float v) {
-    const float p = fast_exp2(fmaxf(v - m, -1e30f) * LOG2E) * inv_z;
-    return (unsigned long long)((double)p * FIX + 0.5);
+  const float fix = inv_z * 1099511627776.0f;
+  auto fixed_mass = [&](float v) {                   // round(p 2^40), split exactly into its two words
+    float x = fast_exp2((v - m) * LOG2E) * fix;
+    x = x < 8388608.0f ? floorf(x + 0.5f) : x;       // from 2^23 on a float is whole
+    if (__builtin_amdgcn_ballot_w64(x >= 4294967296.0f) == 0) return (unsigned long long)(uint32_t)x;   // p < 2^-8: most
+    const float hi = floorf(x * 2.3283064365386963e-10f);
+    return ((unsigned long long)(uint32_t)hi << 32) + (uint32_t)fmaf(hi, -4294967296.0f, x);
   };
-  // the target in the same fixed point, against the mass the row really sums to in it is not needed: p sums to
-  // 1 within rounding, and top_p = 1 is met by the last element at the latest (the search then ends at the
-  // smallest key present)
-  const unsigned long long target = (unsigned long long)((double)top_p * FIX);
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    bin_mass[threadIdx.x] = 0;
-    bin_count[threadIdx.x] = 0;
+  // top_p in the same fixed point; p sums to 1 within rounding, and where that leaves the whole row below the target
+  // the cut is the smallest logit that still carries probability (masked tokens, -inf, are never part of a nucleus)
+  const unsigned long long target = (unsigned long long)((double)top_p * 1099511627776.0);
+  auto add = [&](int bin, float v) {
+    const unsigned long long x = fixed_mass(v);
+    atomicAdd(&bins[bin], wide ? x : x + (1ull << NUC_COUNT_SHIFT));
+    if (wide) atomicAdd(&wide_count[bin], 1u);
+  };
+  auto first_bin = [&](float v) { return min((int)((m - v) * (NUC_BINS / 32.0f)), NUC_BINS - 1); };
+  each_value([&](float v) { add(first_bin(v), v); });
+
+  unsigned long long above = 0;                      // what lies above the bins: mass and count
+  uint32_t count_above = 0;
+  // Finds the bin the target falls into (the last one with any mass if none does); leaves it in sh_*.
+  auto find = [&]() {
     __syncthreads();
-    const uint32_t prefix = sh_prefix;
-    const uint32_t pmask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
-    auto add = [&](float v) {
-      const uint32_t key = order_key(v);
-      if ((key & pmask) != prefix) return;
-      const int b = (key >> shift) & 255;
-      atomicAdd(&bin_mass[b], fixed_mass(v));
-      atomicAdd(&bin_count[b], 1u);
-    };
-    for (int c = threadIdx.x; c < n_vec; c += 256) {
-      float v[VEC];
-      load(c, v);
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) add(v[i]);
+    static_assert(NUC_BINS == 2 * NUC_THREADS, "a lane sums two bins");
+    const int b0 = wave * 128 + lane * 2;
+    const ulonglong2 two = *reinterpret_cast<const ulonglong2*>(bins + b0);
+    const unsigned long long mask = wide ? ~0ull : (1ull << NUC_COUNT_SHIFT) - 1;
+    const unsigned long long m0 = two.x & mask, m1 = two.y & mask;
+    const uint32_t c0 = wide ? wide_count[b0] : (uint32_t)(two.x >> NUC_COUNT_SHIFT);
+    const uint32_t c1 = wide ? wide_count[b0 + 1] : (uint32_t)(two.y >> NUC_COUNT_SHIFT);
+    unsigned long long sm = m0 + m1;                 // inclusive prefixes over the lanes
+    uint32_t sc = c0 + c1;
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned long long tm = __shfl_up(sm, o);
+      const uint32_t tc = __shfl_up(sc, o);
+      if (lane >= o) {
+        sm += tm;
+        sc += tc;
+      }
     }
-    for (int64_t e = (int64_t)n_vec * VEC + threadIdx.x; e < vocab; e += 256) add(tail_value(e));
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      unsigned long long acc = sh_mass_above;
-      unsigned int cnt = sh_count_above;
-      int b = -1, last = -1;
-      unsigned long long acc_last = acc;             // the sums as they stood before bin `last` was added
-      unsigned int cnt_last = cnt;
-      for (int t = 255; t >= 0; --t) {
-        if (bin_count[t] == 0) continue;
-        if (acc + bin_mass[t] >= target) {
-          b = t;
-          break;
-        }
-        if (bin_mass[t] > 0 || last < 0) {           // the smallest keys that still carry probability
-          last = t;
-          acc_last = acc;
-          cnt_last = cnt;
-        }
-        acc += bin_mass[t];
-        cnt += bin_count[t];
-      }
-      if (b < 0) {                                   // rounding left the whole row below the target (top_p ~ 1): the cut
-        b = last < 0 ? 0 : last;                     // is the smallest key that carries probability (masked tokens,
-        acc = acc_last;                              // -inf, are never part of a nucleus)
-        cnt = cnt_last;
-      }
-      sh_mass_above = acc;
-      sh_count_above = cnt;
-      sh_prefix = prefix | ((uint32_t)b << shift);
+    const unsigned long long pos = __builtin_amdgcn_ballot_w64(m0 + m1 > 0);
+    if (lane == 63) {
+      w_mass[wave] = sm;
+      w_count[wave] = sc;
+      w_last[wave] = pos ? 1u : 0u;
     }
     __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    // the prefix is now one key: bin_count / bin_mass of its last-pass bin are its holders
-    const uint32_t key = sh_prefix;
-    const int b = key & 255;
-    const unsigned int holders = bin_count[b];
-    const unsigned long long each = holders ? bin_mass[b] / holders : 0;
-    unsigned long long acc = sh_mass_above;
-    unsigned int need = holders;
-    if (each > 0 && acc < target) {
-      const unsigned long long want = (target - acc + each - 1) / each;
-      need = want < holders ? (unsigned int)want : holders;
-    } else if (acc >= target) {
-      need = 0;                                      // cannot happen: the bin was chosen because acc < target
+    unsigned long long before = above, total = above;
+    uint32_t cbefore = count_above;
+    int last_wave = 0;
+#pragma unroll 1
+    for (int w = 0; w < NUC_THREADS / 64; ++w) {     // (unrolled, its 64 registers of LDS reads push the row out)
+      if (w < wave) {
+        before += w_mass[w];
+        cbefore += w_count[w];
+      }
+      total += w_mass[w];
+      if (w_last[w]) last_wave = w;
+    }
+    const bool reached = total >= target;
+    // exclusive values of this lane's two bins
+    const unsigned long long e0 = before + sm - m0 - m1, e1 = e0 + m0;
+    const uint32_t f0 = cbefore + sc - c0 - c1, f1 = f0 + c0;
+    bool take0, take1;
+    if (reached) {
+      take0 = e0 < target && e0 + m0 >= target;
+      take1 = e1 < target && e1 + m1 >= target;
+    } else {
+      const bool mine = wave == last_wave && pos && lane == 63 - __builtin_clzll(pos);
+      take1 = mine && m1 > 0;
+      take0 = mine && !take1;
+    }
+    if (take0 || take1) {
+      sh_bin = b0 + (take1 ? 1 : 0);
+      sh_above = take1 ? e1 : e0;
+      sh_count_above = take1 ? f1 : f0;
+      sh_bin_mass = take1 ? m1 : m0;
+      sh_bin_count = take1 ? c1 : c0;
+    }
+    if (tid == 0) {
+      sh_lo = 0xFFFFFFFFu;
+      sh_hi = 0;
+      n_list = 0;
+    }
+    __syncthreads();
+    above = sh_above;
+    count_above = sh_count_above;
+    return reached;
+  };
+  auto finish = [&](uint32_t key, unsigned long long group_mass, uint32_t holders, unsigned long long acc, uint32_t cnt) {
+    const unsigned long long one = holders ? group_mass / holders : 0;
+    uint32_t need = holders;
+    if (one > 0 && acc < target) {
+      const unsigned long long want = (target - acc + one - 1) / one;
+      need = want < holders ? (uint32_t)want : holders;
     }
     if (need == 0) need = 1;
-    count[row] = (int32_t)(sh_count_above + need);
-    if (mass) mass[row] = (float)((double)(acc + each * need) / FIX);
+    count[row] = (int32_t)(cnt + need);
+    if (mass) mass[row] = (float)((double)(acc + one * need) * (1.0 / 1099511627776.0));
     if (cut_logit) cut_logit[row] = key_value(key);
+  };
+
+  bool reached = find();
+  uint32_t lo = 0, hi = 0xFFFFFFFFu;                 // keys of the bin's entries, once they have been asked for
+  const int bin0 = (int)sh_bin;
+  bool by_key = false;                               // membership: by first_bin == bin0, then by lo <= key <= hi
+  while (sh_bin_count > NUC_CAP) {                   // block-uniform
+    uint32_t mn = 0xFFFFFFFFu, mx = 0;
+    each_value([&](float v) {
+      const uint32_t key = order_key(v);
+      if (by_key ? key >= lo && key <= hi : first_bin(v) == bin0) {
+        mn = min(mn, key);
+        mx = max(mx, key);
+      }
+    });
+    for (int o = 32; o > 0; o >>= 1) {
+      mn = min(mn, (uint32_t)__shfl_xor(mn, o));
+      mx = max(mx, (uint32_t)__shfl_xor(mx, o));
+    }
+    if (lane == 0) {
+      atomicMin(&sh_lo, mn);
+      atomicMax(&sh_hi, mx);
+    }
+    for (int i = tid; i < NUC_BINS; i += NUC_THREADS) {
+      bins[i] = 0;
+      wide_count[i] = 0;
+    }
+    __syncthreads();
+    lo = sh_lo;
+    hi = sh_hi;
+    by_key = true;
+    if (lo == hi) {                                  // one logit, many holders
+      if (tid == 0) finish(lo, sh_bin_mass, sh_bin_count, above, count_above);
+      return;
+    }
+    int shift = 0;
+    while (((hi - lo) >> shift) >= NUC_BINS) ++shift;
+    each_value([&](float v) {
+      const uint32_t key = order_key(v);
+      if (key >= lo && key <= hi) add((int)((hi - key) >> shift), v);
+    });
+    reached = find();
+    const uint32_t top = hi - (sh_bin << shift);
+    if (shift == 0) {
+      if (tid == 0) finish(top, sh_bin_mass, sh_bin_count, above, count_above);
+      return;
+    }
+    const uint32_t width = (1u << shift) - 1u;
+    lo = top - lo > width ? top - width : lo;
+    hi = top;
   }
+  each_value([&](float v) {
+    const uint32_t key = order_key(v);
+    if (by_key ? key >= lo && key <= hi : first_bin(v) == bin0) {
+      const int at = atomicAdd(&n_list, 1);
+      l_key[at] = key;
+      l_mass[at] = fixed_mass(v);
+    }
+  });
+  __syncthreads();
+  const int n = n_list;
+  if (tid >= n) return;
+  const uint32_t key = l_key[tid];
+  unsigned long long acc = above, group = 0;
+  uint32_t cnt = count_above, holders = 0;
+  bool lower = false;                                // an entry below this one carries probability
+  for (int e = 0; e < n; ++e) {
+    const uint32_t ke = l_key[e];
+    const unsigned long long me = l_mass[e];
+    if (ke > key) {
+      acc += me;
+      ++cnt;
+    } else if (ke == key) {
+      group += me;
+      ++holders;
+    } else {
+      lower = lower || me > 0;
+    }
+  }
+  if (reached ? acc < target && acc + group >= target : group > 0 && !lower)   // its holders agree: same values
+    finish(key, group, holders, acc, cnt);
 }
 
 hipError_t launch_nucleus(const void* logits, int dtype, int64_t rows, int64_t vocab, int64_t stride, float top_p,
                           int32_t* count, float* mass, float* cut_logit, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
+  const unsigned grid = (unsigned)rows;
   if (dtype == 1)
-    nucleus_kernel<true><<<(unsigned)rows, 256, 0, s>>>(logits, vocab, stride, top_p, count, mass, cut_logit);
+    nucleus_kernel<true><<<grid, NUC_THREADS, 0, s>>>(logits, vocab, stride, top_p, count, mass, cut_logit);
   else
-    nucleus_kernel<false><<<(unsigned)rows, 256, 0, s>>>(logits, vocab, stride, top_p, count, mass, cut_logit);
+    nucleus_kernel<false><<<grid, NUC_THREADS, 0, s>>>(logits, vocab, stride, top_p, count, mass, cut_logit);
   return hipGetLastError();
 }
 
