@@ -341,6 +341,8 @@ struct Plan {
   int32_t T, R, R_all;      // chunk tokens, draft rows, LM-head rows (drafts + last-uncached rows)
   const int32_t *d_cu_keys, *d_imp_items;   // importance-score blocks: prefix sums of L_i + chunk_i; (request, first key)
   int32_t n_imp_items, total_keys;
+  const int32_t* d_cu_win;  // append only: prefix sums of the pages each request's rows touch
+  int32_t n_win;
   int slot;
 };
 
@@ -544,6 +546,17 @@ static int32_t build_plan(synera_ctx* c, int32_t B, const int32_t* ctx_len, cons
     p.d_shares = reinterpret_cast<const AttnShare*>(d + o_shares);
     p.d_cuts = reinterpret_cast<const AttnCut*>(d + o_cuts);
     at = o_prog + n_pos * 4;
+  }
+  if (!with_attention) {
+    const size_t o_win = region((size_t)B + 1);
+    int32_t n_win = 0;
+    for (int i = 0; i < B; ++i) {
+      h[o_win + i] = n_win;
+      n_win += (ctx_len[i] + n_draft[i] - 1) / SYNERA_PAGE_SIZE - ctx_len[i] / SYNERA_PAGE_SIZE + 1;
+    }
+    h[o_win + B] = n_win;
+    p.d_cu_win = d + o_win;
+    p.n_win = n_win;
   }
   if (at * 4 > c->meta_cap) return SYNERA_ENOSPC;
   p.slot = slot;
@@ -988,9 +1001,9 @@ extern "C" int32_t synera_kv_append(synera_ctx* c, int32_t layer, int32_t B, con
   if (st != SYNERA_OK) return st;
   const int Hkv = c->desc.n_kv_heads, hd = c->desc.head_dim;
   const size_t layer_elems = (size_t)n_pages_in_pool * Hkv * SY_PAGE * hd;
-  const hipError_t e = launch_kv_append(static_cast<const bf16_t*>(d_k), static_cast<const bf16_t*>(d_v), p.meta, B,
-                                        static_cast<bf16_t*>(d_k_pool) + (size_t)layer * layer_elems,
-                                        static_cast<bf16_t*>(d_v_pool) + (size_t)layer * layer_elems, p.T, Hkv, hd, s);
+  const hipError_t e = launch_kv_append(static_cast<const bf16_t*>(d_k), static_cast<const bf16_t*>(d_v), p.meta, p.d_cu_win,
+                                        p.n_win, B, static_cast<bf16_t*>(d_k_pool) + (size_t)layer * layer_elems,
+                                        static_cast<bf16_t*>(d_v_pool) + (size_t)layer * layer_elems, Hkv, hd, s);
   if (e != hipSuccess) (void)hipGetLastError();
   const int32_t fin = finish_call(c, p, s);      // the upload is queued either way: the slot is busy
   return e != hipSuccess ? SYNERA_EHIP : fin;
