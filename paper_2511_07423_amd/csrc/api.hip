@@ -869,9 +869,6 @@ extern "C" int32_t synera_importance(synera_ctx* c, int32_t n_pages_in_pool, con
   ImportanceLaunch a;
   a.q = c->q;
   a.q_lo = c->q_lo;
-  a.qf = c->qkv;                 // the QKV projection's fp32 buffer is free between verifies
-  a.T = c->last.T;
-  a.total_keys = c->last.total_keys;
   a.k_layer = static_cast<const bf16_t*>(d_k_pool) + (size_t)(m.n_layers - 1) * layer_elems;
   a.row_ml = c->row_ml;
   a.ctx_len = c->last.ctx_len;
@@ -885,8 +882,11 @@ extern "C" int32_t synera_importance(synera_ctx* c, int32_t n_pages_in_pool, con
   a.Hkv = m.n_kv_heads;
   a.hd = m.head_dim;
   a.importance = d_importance;
-  a.parts = c->gparts;           // the projections' K-slice buffer is free between verifies, like qkv
-  a.parts_cap = c->gpart_elems * SY_MAX_K_SLICES;
+  a.parts = c->gparts;           // the projections' K-slice buffer is free between verifies
+  a.parts_cap = c->gpart_elems * SY_MAX_K_SLICES / 2;
+  a.records = reinterpret_cast<int32_t*>(c->gparts + a.parts_cap);
+  a.records_cap = a.parts_cap;
+  a.blocks = c->attn_blocks;
   HIP_TRY(launch_importance(a, s));
   HIP_TRY(launch_importance_dispatch(d_importance, c->last.cu_keys, c->last.ctx_len, c->last.n_unc, c->last.cu_draft,
                                      c->last.B, i_th, theta, d_mean_importance, d_p_imp, s));

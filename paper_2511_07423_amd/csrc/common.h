@@ -8,6 +8,7 @@
 typedef uint16_t bf16_t;  // raw bf16 bits in memory
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 #define SY_PAGE 16
@@ -150,7 +151,6 @@ hipError_t launch_attention(const AttnLaunch& a, hipStream_t s);
 struct ImportanceLaunch {
   const bf16_t* q;           // [T][Hq][hd] (hi, lo)
   const bf16_t* q_lo;
-  float* qf;                 // scratch [T][Hq][hd]: the queries recombined to fp32
   const bf16_t* k_layer;
   const float2* row_ml;      // [T][Hq]
   const int32_t* ctx_len;    // device [B]
@@ -158,10 +158,13 @@ struct ImportanceLaunch {
   const int32_t* block_table;// device [B][max_pages]
   const int32_t* cu_keys;    // device [B+1]: prefix sums of L_i + chunk_i (output offsets)
   const int32_t* items;      // device [n_items][2]: request, first key of the block's 256 keys
-  int32_t n_items, max_pages, T, Hq, Hkv, hd, total_keys;
+  int32_t n_items, max_pages, Hq, Hkv, hd;
   float* importance;         // [cu_keys[B]]
   float* parts;              // scratch: the Hkv shares of a pass's items, [Hkv][items][256]
   size_t parts_cap;          // floats
+  int32_t* records;          // scratch: 24 words per item
+  size_t records_cap;        // words
+  int32_t blocks;            // persistent blocks to launch (two per compute unit)
 };
 hipError_t launch_importance(const ImportanceLaunch& a, hipStream_t s);
 // mean score of each request's draft positions and P_imp of it (Section 4.2, second equation)
