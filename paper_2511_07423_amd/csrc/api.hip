@@ -109,6 +109,7 @@ struct synera_ctx {
   float* part_o;
   float* part_ml;
   float2* row_ml;              // [max_tokens][Hq] softmax statistics of the last layer's attention rows
+  int32_t* imp_records;        // synera_importance: one record per item of the batch
   // batch of the last synera_verify, for synera_importance: device pointers into that call's metadata slot
   struct {
     const int32_t *ctx_len, *cu_tok, *block_table, *cu_keys, *items, *n_unc, *cu_draft;
@@ -263,6 +264,7 @@ extern "C" int32_t synera_create(synera_ctx** out, const synera_model_desc* desc
   const size_t o_pml = take(c->part_cap * 64 * 2 * 4);
   const size_t o_rml = take(T * (size_t)m.n_q_heads * 8);
   c->gpart_elems = T * std::max<size_t>(qkv_dim, (size_t)m.d_model);
+  const size_t o_rec = take((size_t)max_batch * ((size_t)max_pages / 16 + 2) * SY_IMP_RECORD * 4);
   const size_t o_gp = take(SY_MAX_K_SLICES * c->gpart_elems * 4);
   if (hipMalloc(reinterpret_cast<void**>(&c->arena), off) != hipSuccess) {
     (void)hipGetLastError();
@@ -289,6 +291,7 @@ extern "C" int32_t synera_create(synera_ctx** out, const synera_model_desc* desc
   c->part_o = reinterpret_cast<float*>(c->arena + o_po);
   c->part_ml = reinterpret_cast<float*>(c->arena + o_pml);
   c->row_ml = reinterpret_cast<float2*>(c->arena + o_rml);
+  c->imp_records = reinterpret_cast<int32_t*>(c->arena + o_rec);
   c->last.valid = false;
   c->gparts = reinterpret_cast<float*>(c->arena + o_gp);
 
@@ -883,9 +886,8 @@ extern "C" int32_t synera_importance(synera_ctx* c, int32_t n_pages_in_pool, con
   a.hd = m.head_dim;
   a.importance = d_importance;
   a.parts = c->gparts;           // the projections' K-slice buffer is free between verifies
-  a.parts_cap = c->gpart_elems * SY_MAX_K_SLICES / 2;
-  a.records = reinterpret_cast<int32_t*>(c->gparts + a.parts_cap);
-  a.records_cap = a.parts_cap;
+  a.parts_cap = c->gpart_elems * SY_MAX_K_SLICES;
+  a.records = c->imp_records;
   a.blocks = c->attn_blocks;
   HIP_TRY(launch_importance(a, s));
   HIP_TRY(launch_importance_dispatch(d_importance, c->last.cu_keys, c->last.ctx_len, c->last.n_unc, c->last.cu_draft,

@@ -148,6 +148,7 @@ hipError_t launch_attention(const AttnLaunch& a, hipStream_t s);
 
 // Importance scores (column sums of the attention matrix, mean over query heads) of one layer, from the
 // rotated queries, the K pool and the per-row softmax statistics the attention kernel left.
+#define SY_IMP_RECORD 24     // int32
 struct ImportanceLaunch {
   const bf16_t* q;           // [T][Hq][hd] (hi, lo)
   const bf16_t* q_lo;
@@ -162,8 +163,7 @@ struct ImportanceLaunch {
   float* importance;         // [cu_keys[B]]
   float* parts;              // scratch: the Hkv shares of a pass's items, [Hkv][items][256]
   size_t parts_cap;          // floats
-  int32_t* records;          // scratch: 24 words per item
-  size_t records_cap;        // words
+  int32_t* records;          // scratch: [n_items][SY_IMP_RECORD]
   int32_t blocks;            // persistent blocks to launch (two per compute unit)
 };
 hipError_t launch_importance(const ImportanceLaunch& a, hipStream_t s);

@@ -29,14 +29,13 @@ typedef __attribute__((ext_vector_type(8))) int imp_i32x8;
 typedef __attribute__((ext_vector_type(4))) int imp_i32x4;
 
 // Per item: {key0, n_keys, L, tok0, c, output index of key0, 0, 0} and the 16 pages of its keys (the last one repeated).
-#define IMP_RECORD 24            // int32
 
 __global__ __launch_bounds__(256) void importance_items_kernel(ImportanceLaunch a) {
   const int i = (blockIdx.x * 256 + threadIdx.x) / 16, p = threadIdx.x % 16;
   if (i >= a.n_items) return;
   const int req = a.items[2 * i], key0 = a.items[2 * i + 1];
   const int L = a.ctx_len[req], tok0 = a.cu_tok[req], c = a.cu_tok[req + 1] - tok0;
-  int32_t* rec = a.records + (size_t)i * IMP_RECORD;
+  int32_t* rec = a.records + (size_t)i * SY_IMP_RECORD;
   rec[8 + p] = a.block_table[(size_t)req * a.max_pages + min(key0 / SY_PAGE + p, (L + c - 1) / SY_PAGE)];
   if (p == 0) {
     rec[0] = key0;
@@ -70,14 +69,14 @@ __global__ __launch_bounds__(256, 2) void importance_kernel(ImportanceLaunch a, 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t g_inv = 65536u / (uint32_t)G + 1u;  // x g_inv >> 16 = x / G for rows below 32 x 16
   const int n_units = n_batch * Hkv;
-  const SY_CONST_AS int32_t* records = reinterpret_cast<const SY_CONST_AS int32_t*>((uintptr_t)(a.records + (size_t)item0 * IMP_RECORD));
+  const SY_CONST_AS int32_t* records = reinterpret_cast<const SY_CONST_AS int32_t*>((uintptr_t)(a.records + (size_t)item0 * SY_IMP_RECORD));
 
   struct Unit { imp_i32x8 head; imp_i32x4 pages; };  // scalar registers
   auto record = [&](int u) {                         // heads of an item follow each other; past the end: the last unit
     const int item = min(u, n_units - 1) / Hkv;
     Unit r;
-    r.head = *reinterpret_cast<const SY_CONST_AS imp_i32x8*>(records + (size_t)item * IMP_RECORD);
-    r.pages = *reinterpret_cast<const SY_CONST_AS imp_i32x4*>(records + (size_t)item * IMP_RECORD + 8 + 4 * wave);
+    r.head = *reinterpret_cast<const SY_CONST_AS imp_i32x8*>(records + (size_t)item * SY_IMP_RECORD);
+    r.pages = *reinterpret_cast<const SY_CONST_AS imp_i32x4*>(records + (size_t)item * SY_IMP_RECORD + 8 + 4 * wave);
     return r;
   };
   auto load_k = [&](const Unit& r, int kh, u32x4 (&kr)[4][KL]) {
@@ -205,7 +204,7 @@ __global__ __launch_bounds__(256, 2) void importance_kernel(ImportanceLaunch a, 
 
 // Block = one item (256 keys of a request): score = sum of the Hkv shares, in head order.
 __global__ __launch_bounds__(256) void importance_sum_kernel(ImportanceLaunch a, int item0, int n_batch) {
-  const int32_t* rec = a.records + (size_t)(item0 + blockIdx.x) * IMP_RECORD;
+  const int32_t* rec = a.records + (size_t)(item0 + blockIdx.x) * SY_IMP_RECORD;
   if (rec[0] + (int)threadIdx.x >= rec[1]) return;
   float sum = 0.f;
 #pragma unroll 8
@@ -215,7 +214,7 @@ __global__ __launch_bounds__(256) void importance_sum_kernel(ImportanceLaunch a,
 
 hipError_t launch_importance(const ImportanceLaunch& a, hipStream_t s) {
   if (a.n_items <= 0) return hipSuccess;
-  if (!a.parts || a.parts_cap < (size_t)a.Hkv * 256 || !a.records || a.records_cap < (size_t)a.n_items * IMP_RECORD) return hipErrorInvalidValue;
+  if (!a.parts || a.parts_cap < (size_t)a.Hkv * 256 || !a.records) return hipErrorInvalidValue;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)a.hd);
   importance_items_kernel<<<(a.n_items + 15) / 16, 256, 0, s>>>(a);
   // as many items per pass as the scratch holds shares for (one pass on every workload measured)
