@@ -191,7 +191,7 @@ int32_t synera_debug_gemm_slices(const void* d_a, const void* d_a_lo, const void
  * down projection ran K-split, its slices have been added only to the rows the LM head reads), 1/2 rotated q
  * hi/lo (bf16 [T][Hq*h]), 3/4 attention output hi/lo (fp16 [T][Hq*h], scaled by 64), 5/6 SiLU*mul output
  * hi/lo (fp16 [T][f], scaled by 8).  Where the projection that reads such a pair takes it as one array
- * (synera_debug_gemm_paired's form: its plan has 32-wide stages and no low part is switched off), buffers 3 + 4
+ * (synera_debug_gemm_paired's form: its plan has 32-wide stages, or the batch at most 16 tokens, and no low part is switched off), buffers 3 + 4
  * (5 + 6), which lie back to back, hold that array instead: [T][n / 32][hi 32 | lo 32], read from `which` 3 (5)
  * on.  Errors: EINVAL, ENOSPC (bytes beyond the buffer), EHIP.
  */

@@ -90,6 +90,7 @@ struct synera_ctx {
   // device scratch (one allocation)
   char* arena;
   float* x;
+  float* ss;                   // sums of squares of x's rows, [SY_STREAM_ROWS][SY_STREAM_PARTS] (stream.hip)
   uint16_t* y;      // GEMM inputs travel as scaled fp16 (hi, lo) pairs: *_lo is the low part
   uint16_t* y_lo;
   float* qkv;
@@ -170,7 +171,7 @@ static void size_plan(synera_ctx* c) {
   c->unit_cap = streams + (size_t)c->attn_blocks_cap;
   c->pos_cap = streams * tiles + c->unit_cap * 4 + 2 * (size_t)c->attn_blocks_cap;
   c->part_cap = 2 * (size_t)c->attn_blocks_cap;
-  const size_t meta_ints = (size_t)c->max_batch * 5 + 2 + (size_t)c->max_tokens + (size_t)c->max_rows +
+  const size_t meta_ints = (size_t)c->max_batch * 5 + 2 + 2 * (size_t)c->max_tokens + (size_t)c->max_rows +
                            (size_t)c->max_batch * c->max_pages + c->pos_cap * 4 + c->unit_cap * 8 +
                            (size_t)c->attn_blocks_cap * 4 + c->part_cap * 8 + 128 + ((size_t)c->max_batch + 1) +
                            2 * (size_t)c->max_batch * ((size_t)c->max_pages / 16 + 2);
@@ -259,6 +260,7 @@ extern "C" int32_t synera_create(synera_ctx** out, const synera_model_desc* desc
   const size_t o_ysel = take(R * m.d_model * 2), o_ysell = take(R * m.d_model * 2);
   const size_t o_logits = take(R * (size_t)m.vocab * 4);
   const size_t o_ids = take(R * 4), o_p = take(R * 4), o_h = take(R * 4);
+  const size_t o_ss = take((size_t)SY_STREAM_ROWS * SY_STREAM_PARTS * 4);
   const size_t o_cs = take(T * (m.head_dim / 2) * 8);
   const size_t o_po = take(c->part_cap * 64 * m.head_dim * 4);
   const size_t o_pml = take(c->part_cap * 64 * 2 * 4);
@@ -284,6 +286,7 @@ extern "C" int32_t synera_create(synera_ctx** out, const synera_model_desc* desc
   c->act = reinterpret_cast<uint16_t*>(c->arena + o_act);
   c->ysel = reinterpret_cast<uint16_t*>(c->arena + o_ysel);
   c->logits = reinterpret_cast<float*>(c->arena + o_logits);
+  c->ss = reinterpret_cast<float*>(c->arena + o_ss);
   c->lm_ids = reinterpret_cast<int32_t*>(c->arena + o_ids);
   c->lm_p = reinterpret_cast<float*>(c->arena + o_p);
   c->lm_h = reinterpret_cast<float*>(c->arena + o_h);
@@ -379,7 +382,7 @@ static int32_t build_plan(synera_ctx* c, int32_t B, const int32_t* ctx_len, cons
   h[o_cud + B] = R;
   const size_t o_bt = region((size_t)B * max_pages);
   std::memcpy(h + o_bt, block_table, (size_t)B * max_pages * sizeof(int32_t));
-  size_t o_req = 0, o_sel = 0;
+  size_t o_pos = 0, o_slot = 0, o_sel = 0;
   int32_t R_all = R;
   p.n_shares = p.n_cuts = 0;
   p.d_prog = nullptr;
@@ -387,11 +390,16 @@ static int32_t build_plan(synera_ctx* c, int32_t B, const int32_t* ctx_len, cons
   p.d_shares = nullptr;
   p.d_cuts = nullptr;
   if (with_attention) {
-    o_req = region(T);
+    o_pos = region(T);
+    o_slot = region(T);
     o_sel = region((size_t)R + B);
     for (int i = 0; i < B; ++i) {
       const int u = n_unc[i], base = h[o_cu + i];
-      for (int j = 0; j < u + n_draft[i]; ++j) h[o_req + base + j] = i;
+      for (int j = 0; j < u + n_draft[i]; ++j) {
+        const int pos = ctx_len[i] + j;
+        h[o_pos + base + j] = pos;
+        h[o_slot + base + j] = block_table[(size_t)i * max_pages + pos / SY_PAGE] * SY_PAGE + pos % SY_PAGE;
+      }
       for (int j = 0; j < n_draft[i]; ++j) h[o_sel + h[o_cud + i] + j] = base + u + j;
     }
     for (int i = 0; i < B; ++i) {           // rows of the last uncached tokens follow the draft rows
@@ -575,7 +583,8 @@ static int32_t build_plan(synera_ctx* c, int32_t B, const int32_t* ctx_len, cons
   p.meta.first_row = d + o_first;
   p.meta.n_unc = d + o_unc;
   p.meta.block_table = d + o_bt;
-  p.meta.tok_req = d + o_req;
+  p.meta.tok_pos = d + o_pos;
+  p.meta.tok_slot = d + o_slot;
   p.meta.sel_rows = d + o_sel;
   p.meta.max_pages = max_pages;
   p.T = T;
@@ -614,6 +623,27 @@ static int32_t plan_args(int32_t M, int32_t N, int32_t K, int32_t epilogue, int3
 static bool gemm_takes_pairs(int M, int N, int K, int epi, bool stored) {
   GemmArgs g;
   return plan_args(M, N, K, epi, stored, &g) == SYNERA_OK && gemm_plan_bk(g) == 32;
+}
+
+// One projection of a batch of up to SY_STREAM_ROWS rows; g holds what its epilogue and its input need beside this.
+static int32_t run_stream(StreamArgs g, int epi, const void* a, float a_scale, const void* w0, int r0, const void* w1, int r1,
+                          const void* w2, int r2, void* cbuf, int M, int N, int K, hipStream_t s) {
+  g.a = a;
+  g.w[0] = static_cast<const bf16_t*>(w0);
+  g.w[1] = static_cast<const bf16_t*>(w1);
+  g.w[2] = static_cast<const bf16_t*>(w2);
+  g.w_rows[0] = r0;
+  g.w_rows[1] = r1;
+  g.w_rows[2] = r2;
+  g.c = cbuf;
+  g.M = M;
+  g.N = N;
+  g.K = K;
+  g.epilogue = epi;
+  g.out_scale = 1.0f / ((float)(1 << SY_W_SHIFT) * a_scale);
+  g.c_scale = SY_ACT_SCALE;
+  HIP_TRY(launch_stream(g, s));
+  return SYNERA_OK;
 }
 
 // One projection.  a / a_lo: the fp16 pair of a_scale x activation; a_paired: both in the one array a
@@ -668,8 +698,11 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
   const int qd = Hq * hd, kd = Hkv * hd;
   const int lo_off = c->lo_off;
   const size_t layer_elems = (size_t)n_pages_in_pool * Hkv * SY_PAGE * hd;
-  HIP_TRY(launch_embed(static_cast<const bf16_t*>(c->embed), d_tokens, c->x, T, d, m.vocab, s));
-  HIP_TRY(launch_rope_table(p.meta, c->cs, T, hd, m.rope_base, s));
+  // A batch of up to SY_STREAM_ROWS rows takes the projections of stream.hip, with the kernels between them folded in.  (The
+  // ablation of low parts works on the kernels below.)
+  const bool stream = !lo_off && d <= SY_STREAM_NORM_WIDTH && gemm_streams(T);
+  HIP_TRY(launch_embed(static_cast<const bf16_t*>(c->embed), d_tokens, p.meta, c->x, c->cs, stream ? c->ss : nullptr, T, d,
+                       m.vocab, hd, m.rope_base, s));
 
   AttnLaunch al;
   al.q = c->q;
@@ -693,10 +726,15 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
   // Which projections read their activation pair as one paired array (the producer writes it that way then).  The
   // ablation of low parts works on separate arrays: any of its bits keeps them.
   const bool pair_qkv = !lo_off && gemm_takes_pairs(T, qd + 2 * kd, d, GEMM_STORE_F32, true);
-  const bool pair_o = !lo_off && gemm_takes_pairs(T, d, qd, GEMM_ADD_F32, true);
+  const bool pair_o = stream || (!lo_off && gemm_takes_pairs(T, d, qd, GEMM_ADD_F32, true));
   const bool pair_gu = !lo_off && gemm_takes_pairs(T, 2 * m.d_ffn, d, GEMM_SWIGLU, true);
   const bool pair_down = !lo_off && gemm_takes_pairs(T, d, m.d_ffn, GEMM_ADD_F32, true);
   al.o_paired = pair_o;
+  StreamArgs normed = {}, added = {};        // stream: what the projections of RMSNorm(x), and the residual ones, share
+  normed.ss = c->ss;
+  normed.ss_parts = 1;                       // (the embedding's)
+  normed.eps = m.rms_eps;
+  added.ss_out = c->ss;
 
   // K-split projections leave their slices in c->gparts; the kernel that reads the result next adds them
   // (RMSNorm for the two residual projections, RoPE for QKV).  pend = slices waiting to be added to x.
@@ -706,23 +744,41 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
     const synera_layer_weights& w = c->layers[l];
     bf16_t* k_layer = static_cast<bf16_t*>(d_k_pool) + (size_t)l * layer_elems;
     bf16_t* v_layer = static_cast<bf16_t*>(d_v_pool) + (size_t)l * layer_elems;
-    {
-      StageTimer t(c, SYNERA_STAGE_NORM, s);
-      HIP_TRY(launch_rmsnorm(c->x, c->gparts, pend, x_stride, static_cast<const bf16_t*>(w.attn_norm), nullptr, c->y,
-                             c->y_lo, T, d, m.rms_eps, (lo_off & LO_QKV_IN) != 0, pair_qkv, s));
-      pend = 0;
-    }
-    int qkv_parts = 0;
-    {
-      StageTimer t(c, SYNERA_STAGE_QKV, s);
-      if ((st = run_gemm(c->y, c->y_lo, SY_Y_SCALE, w.wq, qd, w.wk, kd, w.wv, kd, c->qkv, nullptr, T, qd + 2 * kd, d,
-                         GEMM_STORE_F32, s, c->gparts, &qkv_parts, pair_qkv)))
+    if (stream) {
+      StageTimer t(c, SYNERA_STAGE_QKV, s);          // with the norm, the rotary embedding and the append
+      StreamArgs g = normed;
+      g.gain = static_cast<const bf16_t*>(w.attn_norm);
+      g.meta = p.meta;
+      g.cs = c->cs;
+      g.q = c->q;
+      g.q_lo = c->q_lo;
+      g.k_layer = k_layer;
+      g.v_layer = v_layer;
+      g.Hq = Hq;
+      g.Hkv = Hkv;
+      g.hd = hd;
+      if ((st = run_stream(g, STREAM_QKV, c->x, SY_Y_SCALE, w.wq, qd, w.wk, kd, w.wv, kd, nullptr, T, qd + 2 * kd, d, s)))
         return st;
-    }
-    {
-      StageTimer t(c, SYNERA_STAGE_ROPE_APPEND, s);
-      HIP_TRY(launch_rope_append(qkv_parts ? c->gparts : c->qkv, qkv_parts, qkv_stride, c->cs, p.meta, c->q, c->q_lo,
-                                 k_layer, v_layer, T, Hq, Hkv, hd, (lo_off & LO_Q) != 0, s));
+      normed.ss_parts = stream_parts(d);             // from here on the residual projections leave the sums
+    } else {
+      {
+        StageTimer t(c, SYNERA_STAGE_NORM, s);
+        HIP_TRY(launch_rmsnorm(c->x, c->gparts, pend, x_stride, static_cast<const bf16_t*>(w.attn_norm), nullptr, c->y,
+                               c->y_lo, T, d, m.rms_eps, (lo_off & LO_QKV_IN) != 0, pair_qkv, s));
+        pend = 0;
+      }
+      int qkv_parts = 0;
+      {
+        StageTimer t(c, SYNERA_STAGE_QKV, s);
+        if ((st = run_gemm(c->y, c->y_lo, SY_Y_SCALE, w.wq, qd, w.wk, kd, w.wv, kd, c->qkv, nullptr, T, qd + 2 * kd, d,
+                           GEMM_STORE_F32, s, c->gparts, &qkv_parts, pair_qkv)))
+          return st;
+      }
+      {
+        StageTimer t(c, SYNERA_STAGE_ROPE_APPEND, s);
+        HIP_TRY(launch_rope_append(qkv_parts ? c->gparts : c->qkv, qkv_parts, qkv_stride, c->cs, p.meta, c->q, c->q_lo,
+                                   k_layer, v_layer, T, Hq, Hkv, hd, (lo_off & LO_Q) != 0, s));
+      }
     }
     al.k_layer = k_layer;
     al.v_layer = v_layer;
@@ -730,6 +786,26 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
     {
       StageTimer t(c, SYNERA_STAGE_ATTENTION, s);
       HIP_TRY(launch_attention(al, s));
+    }
+    if (stream) {
+      {
+        StageTimer t(c, SYNERA_STAGE_O, s);
+        if ((st = run_stream(added, STREAM_ADD, c->o, SY_O_SCALE, w.wo, d, nullptr, 0, nullptr, 0, c->x, T, d, qd, s))) return st;
+      }
+      {
+        StageTimer t(c, SYNERA_STAGE_GATE_UP, s);    // with the norm
+        StreamArgs g = normed;
+        g.gain = static_cast<const bf16_t*>(w.mlp_norm);
+        if ((st = run_stream(g, STREAM_SWIGLU, c->x, SY_Y_SCALE, w.w_gate, m.d_ffn, w.w_up, m.d_ffn, nullptr, 0, c->act, T,
+                             2 * m.d_ffn, d, s)))
+          return st;
+      }
+      {
+        StageTimer t(c, SYNERA_STAGE_DOWN, s);
+        if ((st = run_stream(added, STREAM_ADD, c->act, SY_ACT_SCALE, w.w_down, d, nullptr, 0, nullptr, 0, c->x, T, d, m.d_ffn, s)))
+          return st;
+      }
+      continue;
     }
     {
       StageTimer t(c, SYNERA_STAGE_O, s);
@@ -760,9 +836,9 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
 
   // LM head over the draft rows (plus the last uncached row of requests that have one).
   const bool extra = p.R_all > p.R;
-  // (the last down projection's slices are added here, for the selected rows only)
-  HIP_TRY(launch_rmsnorm(c->x, c->gparts, pend, x_stride, static_cast<const bf16_t*>(c->final_norm), p.meta.sel_rows,
-                         c->ysel, c->ysel_lo, p.R_all, d, m.rms_eps, (lo_off & LO_LM_HEAD_IN) != 0, false, s));
+  if (!stream)   // (the last down projection's slices are added here, for the selected rows only)
+    HIP_TRY(launch_rmsnorm(c->x, c->gparts, pend, x_stride, static_cast<const bf16_t*>(c->final_norm), p.meta.sel_rows,
+                           c->ysel, c->ysel_lo, p.R_all, d, m.rms_eps, (lo_off & LO_LM_HEAD_IN) != 0, false, s));
   float* logits = (d_logits && !extra) ? d_logits : c->logits;
   {
     StageTimer t(c, SYNERA_STAGE_LM_HEAD, s);
@@ -770,7 +846,14 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
     // level, instead of being carried through the layers (measured: dropping this low part leaves max |dlogit| of
     // the 8B ragged batch at its 9e-3; dropping any other site's costs 2e-3 .. 9e-2).
     const uint16_t* ysel_lo = (c->lo_off & SYNERA_LO_KEEP_LM_HEAD) ? c->ysel_lo : nullptr;
-    if ((st = run_gemm(c->ysel, ysel_lo, SY_Y_SCALE, c->lm_head, m.vocab, nullptr, 0, nullptr, 0, logits, nullptr,
+    if (stream) {
+      StreamArgs g = normed;
+      g.gain = static_cast<const bf16_t*>(c->final_norm);
+      g.rows = p.meta.sel_rows;
+      if ((st = run_stream(g, STREAM_LOGITS, c->x, SY_Y_SCALE, c->lm_head, m.vocab, nullptr, 0, nullptr, 0, logits, p.R_all,
+                           m.vocab, d, s)))
+        return st;
+    } else if ((st = run_gemm(c->ysel, ysel_lo, SY_Y_SCALE, c->lm_head, m.vocab, nullptr, 0, nullptr, 0, logits, nullptr,
                        p.R_all, m.vocab, d, GEMM_STORE_F32, s)))
       return st;
   }

@@ -47,7 +47,8 @@ struct BatchMeta {        // device pointers into one uploaded metadata blob (al
   const int32_t* ctx_len;      // [B]
   const int32_t* cu_tok;       // [B+1] prefix sums of chunk lengths (u_i + k_i)
   const int32_t* block_table;  // [B][max_pages]
-  const int32_t* tok_req;      // [T] request of each flattened chunk token
+  const int32_t* tok_pos;      // [T] position of each flattened chunk token in its sequence
+  const int32_t* tok_slot;     // [T] where it goes in the cache: page * SY_PAGE + slot
   const int32_t* sel_rows;     // [R'] chunk-token index feeding LM-head row r
   const int32_t* cu_draft;     // [B+1] prefix sums of k_i (output row offsets)
   const int32_t* first_row;    // [B] LM-head row of the last uncached token, or -1
@@ -55,8 +56,8 @@ struct BatchMeta {        // device pointers into one uploaded metadata blob (al
   int32_t max_pages;
 };
 
-hipError_t launch_embed(const bf16_t* embed, const int32_t* tokens, float* x, int T, int d, int vocab,
-                        hipStream_t s);
+hipError_t launch_embed(const bf16_t* embed, const int32_t* tokens, const BatchMeta& m, float* x, float2* cs, float* ss, int T,
+                        int d, int vocab, int head_dim, float base, hipStream_t s);
 // parts / n_parts: pending K-split slices [n_parts][T][d] of the projection that feeds the residual; the
 // kernel adds them to x first (and writes x back), so the GEMM needs no atomics.  n_parts = 0: none.
 // y_hi / y_lo: the normalised rows as an fp16 pair scaled by SY_Y_SCALE (lo_off: the low part is written as zeros);
@@ -64,7 +65,6 @@ hipError_t launch_embed(const bf16_t* embed, const int32_t* tokens, float* x, in
 hipError_t launch_rmsnorm(float* x, const float* parts, int n_parts, size_t part_stride, const bf16_t* gain,
                           const int32_t* rows, uint16_t* y_hi, uint16_t* y_lo, int n_rows, int d, float eps,
                           bool lo_off, bool paired, hipStream_t s);
-hipError_t launch_rope_table(const BatchMeta& m, float2* cs, int T, int head_dim, float base, hipStream_t s);
 // n_parts > 0: qkv points at K-split slices [n_parts][T][(Hq+2Hkv) hd] whose sum is the projection.
 hipError_t launch_rope_append(const float* qkv, int n_parts, size_t part_stride, const float2* cs, const BatchMeta& m,
                               bf16_t* q_hi, bf16_t* q_lo, bf16_t* k_layer, bf16_t* v_layer, int T, int Hq, int Hkv,
@@ -205,3 +205,37 @@ hipError_t launch_proj_nf4_low(int mt, const GemmArgs& g, hipStream_t s);    // 
 hipError_t launch_proj_nf4_high(int mt, const GemmArgs& g, hipStream_t s);   // 256 columns, 160 .. 272 rows
 hipError_t launch_proj_nf2(int mt, const GemmArgs& g, hipStream_t s);        // 128 columns, 16 .. 192 rows
 hipError_t launch_proj_k64(int mt, int nf, const GemmArgs& g, hipStream_t s);   // BK = 64: 128 columns x 16 .. 144 rows, 256 x 16 .. 80
+
+// ---------------------------------------------------------------- stream.hip
+// The projections of a batch of up to SY_STREAM_ROWS rows.
+enum StreamEpilogue {
+  STREAM_LOGITS = 0,     // c = product
+  STREAM_ADD = 1,        // c += product, and the sums of squares of the new c
+  STREAM_SWIGLU = 2,     // w[0] = gate, w[1] = up; c = the fp16 pair of c_scale x SiLU(gate) up, as one paired array
+  STREAM_QKV = 3         // w = Wq, Wk, Wv: rotated q to a bf16 pair, rotated k and v to the tokens' pages
+};
+#define SY_STREAM_ROWS 16
+#define SY_STREAM_NORM_WIDTH 8192   // widest row the kernels normalise (its gains and row sums must fit their LDS)
+#define SY_STREAM_PARTS 256         // parts a row's sum of squares may come in; the pitch of their array
+struct StreamArgs {
+  const void* a;         // ADD: the paired array [M][K / 32][hi 32 | lo 32]; else x, f32 [..][K], which RMSNorm is applied to
+  const int32_t* rows;   // LOGITS: the row of x that is row m
+  const float* ss;       // not for ADD: sums of squares of the rows of x, [..][SY_STREAM_PARTS], the first ss_parts valid
+  const bf16_t* gain;    // not for ADD
+  float* ss_out;         // ADD: the same of the new c, stream_parts(N) parts
+  int32_t ss_parts;
+  float eps;
+  const bf16_t* w[3];
+  int32_t w_rows[3];     // multiples of 8; unused = 0
+  void* c;               // f32 [M][N]; SwiGLU: [M][N / 2 / 32][hi 32 | lo 32]
+  int32_t M, N, K;       // N: weight rows in all (gate + up for SwiGLU)
+  int32_t epilogue, half_units;
+  float out_scale, c_scale;   // as in GemmArgs
+  BatchMeta meta;        // QKV only, and below
+  const float2* cs;
+  bf16_t *q, *q_lo, *k_layer, *v_layer;
+  int32_t Hq, Hkv, hd;
+};
+hipError_t launch_stream(StreamArgs g, hipStream_t s);
+int stream_parts(int N);    // parts an ADD launch of N weight rows leaves
+bool gemm_streams(int M);   // whether launch_stream takes a batch of M rows (no tile is forced)

@@ -4,31 +4,48 @@
 // any roofline that matters; they are written for coalesced 16-byte accesses.
 #include "common.h"
 
-// ------------------------------------------------------------------ embedding
-// x[t][:] = float(E[token[t]][:]).  One block per token.  Token ids live on the device and cannot
-// be validated by the host: an id outside [0, vocab) is clamped into the table instead of being
-// followed out of bounds.
+// ------------------------------------------------------------------ embedding, rotary table
+// x[t][:] = float(E[token[t]][:]) and cs[t][i] = (cos, sin)(pos_t * base^(-2i/hd)), angle formed in double; ss (optional): the
+// row's sum of squares as the first of its SY_STREAM_PARTS parts.  One block per token.  Token ids live on the device and
+// cannot be validated by the host: an id outside [0, vocab) is clamped into the table instead of being followed out of
+// bounds.  (Two kernels in one: each takes 4 us, nearly all of it latency, and their loads do not depend on each other.)
 __global__ __launch_bounds__(256) void embed_kernel(const bf16_t* __restrict__ embed,
-                                                    const int32_t* __restrict__ tokens,
-                                                    float* __restrict__ x, int d, int vocab) {
+                                                    const int32_t* __restrict__ tokens, BatchMeta m,
+                                                    float* __restrict__ x, float2* __restrict__ cs,
+                                                    float* __restrict__ ss, int d, int vocab, int half, float base) {
   const int t = blockIdx.x;
   int tok = tokens[t];
+  const int pos = m.tok_pos[t];
   tok = tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok);
   const bf16_t* src = embed + (size_t)tok * d;
   float* dst = x + (size_t)t * d;
+  float sum = 0.f;
   for (int c = threadIdx.x * 8; c < d; c += 256 * 8) {
     uint4 v = *reinterpret_cast<const uint4*>(src + c);
     float4 lo = {bf2f(v.x & 0xFFFF), bf2f(v.x >> 16), bf2f(v.y & 0xFFFF), bf2f(v.y >> 16)};
     float4 hi = {bf2f(v.z & 0xFFFF), bf2f(v.z >> 16), bf2f(v.w & 0xFFFF), bf2f(v.w >> 16)};
     *reinterpret_cast<float4*>(dst + c) = lo;
     *reinterpret_cast<float4*>(dst + c + 4) = hi;
+    sum += lo.x * lo.x + lo.y * lo.y + lo.z * lo.z + lo.w * lo.w + hi.x * hi.x + hi.y * hi.y + hi.z * hi.z + hi.w * hi.w;
   }
+  for (int i = threadIdx.x; i < half; i += 256) {
+    const double ang = (double)pos * pow((double)base, -(double)i / (double)half);
+    double sn, cn;
+    sincos(ang, &sn, &cn);
+    cs[(size_t)t * half + i] = make_float2((float)cn, (float)sn);
+  }
+  if (!ss) return;
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  __shared__ float red[4];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) ss[(size_t)t * SY_STREAM_PARTS] = red[0] + red[1] + red[2] + red[3];
 }
 
-hipError_t launch_embed(const bf16_t* embed, const int32_t* tokens, float* x, int T, int d, int vocab,
-                        hipStream_t s) {
+hipError_t launch_embed(const bf16_t* embed, const int32_t* tokens, const BatchMeta& m, float* x, float2* cs, float* ss, int T,
+                        int d, int vocab, int head_dim, float base, hipStream_t s) {
   if (T <= 0) return hipSuccess;
-  embed_kernel<<<T, 256, 0, s>>>(embed, tokens, x, d, vocab);
+  embed_kernel<<<T, 256, 0, s>>>(embed, tokens, m, x, cs, ss, d, vocab, head_dim / 2, base);
   return hipGetLastError();
 }
 
@@ -161,31 +178,11 @@ hipError_t launch_rmsnorm(float* x, const float* parts, int n_parts, size_t part
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ rotary table
-// cs[t][i] = (cos, sin)(pos_t * base^(-2i/hd)), angle formed in double.
-__global__ void rope_table_kernel(BatchMeta m, float2* __restrict__ cs, int T, int half, float base) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= T * half) return;
-  const int t = idx / half, i = idx % half;
-  const int r = m.tok_req[t];
-  const int pos = m.ctx_len[r] + (t - m.cu_tok[r]);
-  const double ang = (double)pos * pow((double)base, -(double)i / (double)half);
-  double sn, cn;
-  sincos(ang, &sn, &cn);
-  cs[idx] = make_float2((float)cn, (float)sn);
-}
-
-hipError_t launch_rope_table(const BatchMeta& m, float2* cs, int T, int head_dim, float base, hipStream_t s) {
-  const int n = T * (head_dim / 2);
-  if (n <= 0) return hipSuccess;
-  rope_table_kernel<<<(n + 255) / 256, 256, 0, s>>>(m, cs, T, head_dim / 2, base);
-  return hipGetLastError();
-}
-
 // ------------------------------------------------------------------ rotary + append
 // One block per chunk token.  Input row: fp32 [q heads | k heads | v heads] x hd.
 // q and k are rotated on adjacent pairs; q goes to a bf16 (hi, lo) pair [T][Hq][hd]; k and v go to
-// the token's page (position t lives in page block_table[t/16], slot t%16):
+// the token's page and slot, which the host has looked up (through request, length and block table it is a chain of four
+// loads for every block):
 // K page [kv_head][slot][dim], V page [kv_head][dim][slot].
 __global__ __launch_bounds__(256) void rope_append_kernel(const float* __restrict__ qkv, int n_parts,
                                                           size_t part_stride,
@@ -194,10 +191,7 @@ __global__ __launch_bounds__(256) void rope_append_kernel(const float* __restric
                                                           bf16_t* __restrict__ k_layer, bf16_t* __restrict__ v_layer,
                                                           int Hq, int Hkv, int hd, bool lo_off) {
   const int t = blockIdx.x;
-  const int r = m.tok_req[t];
-  const int pos = m.ctx_len[r] + (t - m.cu_tok[r]);
-  const int page = m.block_table[(size_t)r * m.max_pages + pos / SY_PAGE];
-  const int slot = pos % SY_PAGE;
+  const int page = m.tok_slot[t] / SY_PAGE, slot = m.tok_slot[t] % SY_PAGE;
   const int half = hd / 2;
   const int n_pairs = (Hq + 2 * Hkv) * half;
   const float* row = qkv + (size_t)t * (Hq + 2 * Hkv) * hd;

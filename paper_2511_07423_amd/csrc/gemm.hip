@@ -110,6 +110,11 @@ int gemm_pick_split(const GemmArgs& g) {
   return mt < 0 ? 1 : split;
 }
 
+// Up to 16 rows.  Every block of stream.hip reads all activations beside its own weight rows: at 16 rows twice the bytes of
+// a residual projection's weights (output + down projection of the 8B shape: 33 us at 8 rows, 40 us at 16), at 32 rows four
+// times, where K slices over blocks are the better split.
+bool gemm_streams(int M) { return M <= SY_STREAM_ROWS && g_forced < 0; }
+
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0) return hipSuccess;
   if (!g.a || !g.w[0] || !g.c || g.N < 128 || g.K < 64 || g.K % 64 != 0 || g.split_k < 1)
