@@ -110,6 +110,7 @@ struct synera_ctx {
   float* part_o;
   float* part_ml;
   float2* row_ml;              // [max_tokens][Hq] softmax statistics of the last layer's attention rows
+  bool streams;                // whether this model's projections fit stream.hip
   int32_t* imp_records;        // synera_importance: one record per item of the batch
   // batch of the last synera_verify, for synera_importance: device pointers into that call's metadata slot
   struct {
@@ -227,6 +228,11 @@ extern "C" int32_t synera_create(synera_ctx** out, const synera_model_desc* desc
   c->embed = w->embed;
   c->final_norm = w->final_norm;
   c->lm_head = w->lm_head;
+  // stream.hip works in stages of 128 k (d_ffn may be an odd multiple of 64), keeps a normalised row's gains in LDS and
+  // copies them 16 bytes at a time, which RMSNorm's own kernel (8-byte loads) does not need of a pointer.
+  uintptr_t gains = reinterpret_cast<uintptr_t>(w->final_norm);
+  for (const synera_layer_weights& lw : c->layers) gains |= reinterpret_cast<uintptr_t>(lw.attn_norm) | reinterpret_cast<uintptr_t>(lw.mlp_norm);
+  c->streams = m.d_ffn % 128 == 0 && m.d_model <= SY_STREAM_NORM_WIDTH && (gains & 15) == 0;
   c->max_batch = max_batch;
   c->max_tokens = max_tokens;
   c->max_pages = max_pages;
@@ -700,7 +706,7 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
   const size_t layer_elems = (size_t)n_pages_in_pool * Hkv * SY_PAGE * hd;
   // A batch of up to SY_STREAM_ROWS rows takes the projections of stream.hip, with the kernels between them folded in.  (The
   // ablation of low parts works on the kernels below.)
-  const bool stream = !lo_off && d <= SY_STREAM_NORM_WIDTH && gemm_streams(T);
+  const bool stream = !lo_off && c->streams && gemm_streams(T);
   HIP_TRY(launch_embed(static_cast<const bf16_t*>(c->embed), d_tokens, p.meta, c->x, c->cs, stream ? c->ss : nullptr, T, d,
                        m.vocab, hd, m.rope_base, s));
 

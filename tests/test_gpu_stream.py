@@ -58,3 +58,41 @@ def test_small_batch_agrees_with_the_tile_kernels(dims, chunks):
     for a, b in zip(got[1:], tiles[1:]):           # the whole pools, what neither wrote included
         assert ((a[0] - b[0]).abs() <= 2.0 ** -7 * b[0].abs() + 1e-4).all()     # a bf16 rounding apart
         assert ((a[1] - b[1]).abs() <= 2.0 ** -7 * b[1].abs() + 1e-2).all()
+
+
+@pytest.mark.parametrize("d_ffn,shift", [(192, 0), (64, 0), (256, 4)], ids=["ffn192", "ffn64", "gain8"])
+def test_models_outside_the_kernels_forms_take_the_tile_kernels(d_ffn, shift):
+    """An FFN width that is an odd multiple of 64, and RMSNorm gains that start 8 bytes past a 16-byte boundary, are served
+    at every batch size."""
+    import paper_2511_07423_amd as synera
+    shape = wl.ModelShape("stream", 2, 256, 4, 4, 64, d_ffn, 128)
+    head = wl.draw_head_weights(shape, 81, DEV)
+    layers = [wl.draw_layer_weights(shape, 81, l, DEV) for l in range(shape.n_layers)]
+    if shift:                                      # elements of 2 bytes
+        moved = torch.zeros(shape.d_model + 8, dtype=torch.bfloat16, device=DEV)
+        moved[shift: shift + shape.d_model] = layers[1]["mlp_norm"]
+        layers[1]["mlp_norm"] = moved[shift: shift + shape.d_model]
+    ctx, u, k = (np.array([v], np.int32) for v in (20, 1, 4))
+    bt = np.arange(2, dtype=np.int32).reshape(1, 2)
+    toks = torch.arange(5, dtype=torch.int32, device=DEV)
+    anchor = torch.zeros(1, dtype=torch.int32, device=DEV)
+    ver = synera.Verifier(shape, head, layers, max_batch=1, max_tokens=5, max_pages=2)
+
+    def run(tile):
+        g = torch.Generator(device=DEV).manual_seed(82)
+        kp = torch.randn((2, 2, 4, wl.PAGE_SIZE, 64), generator=g, device=DEV).to(torch.bfloat16)
+        vp = torch.randn((2, 2, 4, 64, wl.PAGE_SIZE), generator=g, device=DEV).to(torch.bfloat16)
+        synera.debug_set_gemm_tile(tile)
+        try:
+            out = ver.verify(ctx, u, k, toks, anchor, bt, 2, kp, vp, want_logits=True)
+            torch.cuda.synchronize()
+        finally:
+            synera.debug_set_gemm_tile(-1)
+        return out["logits"].cpu(), kp.cpu(), vp.cpu()
+
+    got, tiles = run(-1), run(101)
+    ver.close()
+    assert all(torch.isfinite(t.float()).all() for t in got)
+    assert (got[0] - tiles[0]).abs().max().item() < 2e-3 * max(tiles[0].abs().max().item(), 1.0)
+    for a, b in zip(got[1:], tiles[1:]):
+        assert ((a[0].float() - b[0].float()).abs() <= 2.0 ** -7 * b[0].float().abs() + 1e-4).all()
