@@ -158,6 +158,33 @@ def test_kv_append_is_bit_exact_and_touches_nothing_else():
     ver.close()
 
 
+def test_kv_append_takes_rows_and_pools_that_start_four_bytes_off():
+    """The kernel moves 16 bytes at a time; rows and pools need only start at a 4-byte boundary."""
+    synera = _synera()
+    shape = _mini_shape()
+    head = wl.draw_head_weights(shape, 9, DEV)
+    layers = [wl.draw_layer_weights(shape, 9, l, DEV) for l in range(shape.n_layers)]
+    start, n_new = np.array([5, 16], np.int32), np.array([30, 33], np.int32)
+    bt = np.arange(8, dtype=np.int32).reshape(2, 4)
+    ver = synera.Verifier(shape, head, layers, max_batch=2, max_tokens=64, max_pages=4)
+    rows, pool = (63, 2, 64), (2, 8, 2, 16, 64)
+    k, v = (wl.draw_normal_bf16(rows, 1.0, s, DEV) for s in (7, 8))
+
+    def run(off):
+        def moved(t):
+            flat = torch.zeros(t.numel() + 8, dtype=torch.bfloat16, device=DEV)
+            flat[off: off + t.numel()] = t.reshape(-1)
+            return flat[off: off + t.numel()].view(t.shape)
+        kp, vp = (moved(torch.full(pool, 3.0, dtype=torch.bfloat16, device=DEV)) for _ in range(2))
+        ver.kv_append(1, start, n_new, moved(k), moved(v), bt, 8, kp, vp.view(2, 8, 2, 64, 16))
+        torch.cuda.synchronize()
+        return kp.cpu(), vp.cpu()
+
+    for a, b in zip(run(0), run(2)):
+        assert torch.equal(a, b)
+    ver.close()
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 128, 64), (16, 256, 256), (130, 384, 512), (128, 4096, 4096),
                                    (544, 1024, 14336), (257, 32000, 256)])
 def test_gemm_matches_float64(M, N, K):
