@@ -254,6 +254,42 @@ def test_a_request_with_nan_in_its_cache_leaves_the_others_untouched(monkeypatch
         assert np.array_equal(clean[name][1:], dirty[name][1:]), name
 
 
+@pytest.mark.parametrize("heads", [(4, 4, 64), (16, 4, 128)], ids=["hd64", "hd128"])
+@pytest.mark.parametrize("ctx,k", [(100, 1), (180, 4), (400, 4), (900, 16), (3000, 4), (6000, 16)])
+def test_streams_cut_over_blocks_merge_to_the_whole(heads, ctx, k):
+    """A lone request's keys cut into anything from one share to dozens (the merge takes eight at a time) against the same
+    verify with at most two blocks in the plan.  A share rounds its probabilities to bf16 pairs (2^-17) against its own
+    reference maximum: 2^-16 sum(p |v|) in o, whose size is that sum over sqrt(keys) or more: 1e-3."""
+    import paper_2511_07423_amd as synera
+    Hq, Hkv, hd = heads
+    shape = wl.ModelShape("cut", 1, 512, Hq, Hkv, hd, 256, 256)
+    head = wl.draw_head_weights(shape, 91, DEV)
+    layers = [wl.draw_layer_weights(shape, 91, 0, DEV)]
+    g = torch.Generator(device=DEV).manual_seed(92)
+    pages = (ctx + k + 15) // 16
+    k_pool = torch.randn((1, pages, Hkv, 16, hd), generator=g, device=DEV).to(torch.bfloat16)
+    v_pool = torch.randn((1, pages, Hkv, hd, 16), generator=g, device=DEV).to(torch.bfloat16)
+    bt = np.random.default_rng(93).permutation(pages).astype(np.int32).reshape(1, pages)
+    args = [np.array([n], np.int32) for n in (ctx, 0, k)]
+    toks = torch.arange(k, dtype=torch.int32, device=DEV)
+    anchor = torch.zeros(1, dtype=torch.int32, device=DEV)
+    ver = synera.Verifier(shape, head, layers, max_batch=1, max_tokens=k, max_pages=pages)
+
+    def run():
+        out = ver.verify(*args, toks, anchor, bt, pages, k_pool, v_pool, want_logits=True)
+        imp = ver.importance(*args, pages, k_pool, i_th=0.05)
+        torch.cuda.synchronize()
+        return out["logits"].cpu().double(), imp["scores"].cpu().double()
+
+    got = run()
+    ver.debug_set_attention_plan(attn_blocks=2)
+    want = run()
+    ver.close()
+    for a, b in zip(got, want):
+        assert torch.isfinite(a).all() and torch.isfinite(b).all()
+        assert (a - b).norm().item() <= 1e-3 * b.norm().item()
+
+
 def test_both_forms_of_the_activation_pair_give_the_same_bits():
     """A projection whose stage holds one 32-wide K block reads its (hi, lo) activations as one array of whole
     128-byte lines, written that way by RMSNorm, by the attention's normalising store and by the SwiGLU epilogue;
