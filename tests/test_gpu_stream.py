@@ -96,3 +96,10 @@ def test_models_outside_the_kernels_forms_take_the_tile_kernels(d_ffn, shift):
     assert (got[0] - tiles[0]).abs().max().item() < 2e-3 * max(tiles[0].abs().max().item(), 1.0)
     for a, b in zip(got[1:], tiles[1:]):
         assert ((a[0].float() - b[0].float()).abs() <= 2.0 ** -7 * b[0].float().abs() + 1e-4).all()
+
+
+@pytest.mark.parametrize("slices", range(1, 9))
+def test_rotary_kernel_adds_every_number_of_slices(slices):
+    """The tile kernels cut K = 256 s into s slices here, and the rotary kernel adds them; the streams have none.  384
+    values per token: its last block of threads is half empty."""
+    test_small_batch_agrees_with_the_tile_kernels((256 * slices, 2, 2, 64, 128, 128), [(37, 3, 4), (15, 0, 5)])
