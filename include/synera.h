@@ -216,7 +216,8 @@ int32_t synera_confidence_topk(const void* d_logits, int32_t dtype, int64_t rows
  * d_count i32 [rows]; d_mass f32 [rows] (NULL to skip) = the probability those tokens hold; d_cut_logit f32
  * [rows] (NULL to skip) = the smallest logit kept: the nucleus is every token above it plus the first
  * count - #{above} holders of it in id order, i.e. the first d_count entries of synera_confidence_topk's order.
- * Logits finite or -inf.  Masses are summed in 40-bit fixed point (order-independent: the count is reproducible);
+ * Logits finite or -inf; a row in which no token has probability (all -inf, or every logit below -1e30) gets all
+ * holders of its largest logit, mass 0.  Masses are summed in 40-bit fixed point (order-independent: the count is reproducible);
  * a running sum that passes within ~1e-6 of top_p may fall either way against an exact evaluation.
  * Errors: EINVAL (top_p outside (0, 1], null pointers, alignment as synera_confidence), EHIP.
  */

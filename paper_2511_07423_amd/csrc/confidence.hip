@@ -455,7 +455,8 @@ hipError_t launch_confidence_topk(const void* logits, int dtype, int64_t rows, i
 // logits down, reaches top_p holds a few dozen entries: they are listed and each sums the masses above itself.  A bin
 // with more than NUC_CAP entries is first cut again by the order-preserving integer keys of its logits, down to a
 // single key if need be (ties).  Masses are 40-bit fixed point: integer sums do not depend on the order in which
-// threads arrive, so the result is reproducible.
+// threads arrive, so the result is reproducible.  A row without any mass (all -inf, or every logit below the running
+// maximum's start of -1e30, as finfo.min masks are) has no cut: its nucleus is the holders of its largest logit, of mass 0.
 // Bound by the one read of the row and, for few rows, by the chain of barriers: 532 x 32000 f32: 176 us with a
 // four-pass radix search over the keys (every entry through two 64-bit LDS atomics on at most a handful of bins),
 // 46 us.
@@ -553,7 +554,8 @@ __global__ __launch_bounds__(NUC_THREADS, 8) void nucleus_kernel(const void* __r
   };
   // top_p in the same fixed point; p sums to 1 within rounding, and where that leaves the whole row below the target
   // the cut is the smallest logit that still carries probability (masked tokens, -inf, are never part of a nucleus)
-  const unsigned long long target = (unsigned long long)((double)top_p * 1099511627776.0);
+  // (a top_p below 2^-40 asks for one token, as the smallest target that a bin with mass can cross does)
+  const unsigned long long asked = (unsigned long long)((double)top_p * 1099511627776.0), target = asked > 0 ? asked : 1;
   auto add = [&](int bin, float v) {
     const unsigned long long x = fixed_mass(v);
     atomicAdd(&bins[bin], wide ? x : x + (1ull << NUC_COUNT_SHIFT));
@@ -564,7 +566,8 @@ __global__ __launch_bounds__(NUC_THREADS, 8) void nucleus_kernel(const void* __r
 
   unsigned long long above = 0;                      // what lies above the bins: mass and count
   uint32_t count_above = 0;
-  // Finds the bin the target falls into (the last one with any mass if none does); leaves it in sh_*.
+  // Finds the bin the target falls into (the last one with any mass if none does, no bin if none has); leaves it in sh_*.
+  // (The target is at least 1: the bin it falls into has mass.)
   auto find = [&]() {
     __syncthreads();
     static_assert(NUC_BINS == 2 * NUC_THREADS, "a lane sums two bins");
@@ -624,6 +627,13 @@ __global__ __launch_bounds__(NUC_THREADS, 8) void nucleus_kernel(const void* __r
       sh_bin_count = take1 ? c1 : c0;
     }
     if (tid == 0) {
+      if (total == above) {                          // no mass in any bin: nobody took one
+        sh_bin = 0;
+        sh_above = above;
+        sh_count_above = count_above;
+        sh_bin_mass = 0;
+        sh_bin_count = 0;
+      }
       sh_lo = 0xFFFFFFFFu;
       sh_hi = 0;
       n_list = 0;
@@ -647,6 +657,21 @@ __global__ __launch_bounds__(NUC_THREADS, 8) void nucleus_kernel(const void* __r
   };
 
   bool reached = find();
+  if (sh_bin_mass == 0) {                            // block-uniform: a row without mass
+    uint32_t top = 0;
+    each_value([&](float v) { top = max(top, order_key(v)); });
+    for (int o = 32; o > 0; o >>= 1) top = max(top, (uint32_t)__shfl_xor(top, o));
+    if (lane == 0) atomicMax(&sh_hi, top);
+    __syncthreads();
+    top = sh_hi;
+    int holders = 0;
+    each_value([&](float v) { holders += order_key(v) == top ? 1 : 0; });
+    for (int o = 32; o > 0; o >>= 1) holders += __shfl_xor(holders, o);
+    if (lane == 0) atomicAdd(&n_list, holders);
+    __syncthreads();
+    if (tid == 0) finish(top, 0, asked > 0 ? (uint32_t)n_list : 1u, 0, 0);
+    return;
+  }
   uint32_t lo = 0, hi = 0xFFFFFFFFu;                 // keys of the bin's entries, once they have been asked for
   const int bin0 = (int)sh_bin;
   bool by_key = false;                               // membership: by first_bin == bin0, then by lo <= key <= hi
@@ -699,12 +724,14 @@ __global__ __launch_bounds__(NUC_THREADS, 8) void nucleus_kernel(const void* __r
     const uint32_t key = order_key(v);
     if (by_key ? key >= lo && key <= hi : first_bin(v) == bin0) {
       const int at = atomicAdd(&n_list, 1);
-      l_key[at] = key;
-      l_mass[at] = fixed_mass(v);
+      if (at < NUC_CAP) {                            // the bin's count says so
+        l_key[at] = key;
+        l_mass[at] = fixed_mass(v);
+      }
     }
   });
   __syncthreads();
-  const int n = n_list;
+  const int n = min(n_list, NUC_CAP);
   if (tid >= n) return;
   const uint32_t key = l_key[tid];
   unsigned long long acc = above, group = 0;

@@ -184,6 +184,41 @@ def test_nucleus_matches_oracle(dtype, rows, vocab):
     assert _check_nucleus(x, 0.05, "clear of ties") + _check_nucleus(x, 0.5, "clear of ties") <= 2
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("vocab", [8, 1037, 32000])
+def test_nucleus_of_rows_without_mass(dtype, vocab):
+    """Rows that no token carries probability in, each behind an ordinary row, outputs filled beforehand: all holders of
+    the largest logit, mass 0; and a top_p too small for the fixed point asks for one token of any row."""
+    from paper_2511_07423_amd import binding
+    low = torch.finfo(dtype).min
+    g = torch.Generator(device=DEV).manual_seed(vocab)
+    wide = (vocab + 7) // 8 * 8
+    x = (torch.randn((10, wide), generator=g, device=DEV) * 3).to(dtype)[:, :vocab]
+    x[1] = float("-inf")
+    x[3] = low
+    x[5] = float("-inf"); x[5, vocab // 2:] = low
+    x[7] = -2e30; x[7, ::3] = -1.5e30; x[7, 0] = float("-inf")
+    x[9] = float("-inf"); x[9, vocab - 1] = 0.0                   # one token alone
+    top = x.float().max(1).values
+    holders = (x.float() == top[:, None]).sum(1).cpu()
+    for top_p in (0.9, 1e-13, 1.0):
+        n = torch.full((10,), -7, dtype=torch.int32, device=DEV)
+        mass, cut = torch.full((10,), -7.0, device=DEV), torch.full((10,), -7.0, device=DEV)
+        st = binding._lib.synera_nucleus(x.data_ptr(), 0 if dtype == torch.float32 else 1, 10, vocab, wide, top_p,
+                                                n.data_ptr(), mass.data_ptr(), cut.data_ptr(), None)
+        torch.cuda.synchronize()
+        assert st == 0
+        for r in (1, 3, 5, 7):
+            assert int(n[r]) == (int(holders[r]) if top_p > 1e-12 else 1), (r, top_p)
+            assert float(mass[r]) == 0.0 and float(cut[r]) == float(top[r]), (r, top_p)
+        assert int(n[9]) == 1 and float(mass[9]) == pytest.approx(1.0, abs=1e-6) and float(cut[9]) == 0.0
+        if top_p < 1e-12:                                         # the largest logit's first holder
+            assert (n[0::2] == 1).all() and torch.equal(cut[0::2], top[0::2])
+            p = torch.softmax(x[0::2].double(), 1).max(1).values
+            assert torch.allclose(mass[0::2].double(), p, rtol=1e-5, atol=0)
+    _check_nucleus(x[0:9:2], 0.9, "ordinary rows")
+
+
 def test_nucleus_ties_one_hot_masked_and_uniform_rows():
     synera = _synera()
     V = 4096
