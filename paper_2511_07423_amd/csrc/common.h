@@ -42,6 +42,13 @@ __device__ __forceinline__ void split_f16x2(float a, float b, uint32_t& hi, uint
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2_t));
 }
 
+// One rotary pair by the angle (c, s).  Both fused operations are spelled out: left to the compiler, either product of a sum may
+// be the one that is rounded first, and a cached K value in many would depend on which kernel wrote it.
+__device__ __forceinline__ void rotate_pair(float v0, float v1, float c, float s, float& r0, float& r1) {
+  r0 = __builtin_fmaf(v0, c, -(v1 * s));
+  r1 = __builtin_fmaf(v1, c, v0 * s);
+}
+
 // ---------------------------------------------------------------- elementwise.hip
 struct BatchMeta {        // device pointers into one uploaded metadata blob (all int32)
   const int32_t* ctx_len;      // [B]

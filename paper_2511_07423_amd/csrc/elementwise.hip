@@ -212,8 +212,9 @@ __global__ __launch_bounds__(256) void rope_append_kernel(const float* __restric
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[r] += part[s][r];
   if (head < Hq + Hkv) {
-    const float r0 = v[0] * c[0] - v[1] * c[1], r1 = v[0] * c[1] + v[1] * c[0];
-    const float r2 = v[2] * c[2] - v[3] * c[3], r3 = v[2] * c[3] + v[3] * c[2];
+    float r0, r1, r2, r3;
+    rotate_pair(v[0], v[1], c[0], c[1], r0, r1);
+    rotate_pair(v[2], v[3], c[2], c[3], r2, r3);
     const uint32_t p0 = pack_bf2(r0, r1), p1 = pack_bf2(r2, r3);
     if (head < Hq) {
       const size_t at = ((size_t)t * Hq + head) * hd + dim;

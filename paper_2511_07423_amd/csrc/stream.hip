@@ -325,8 +325,9 @@ __global__ __launch_bounds__(64 * WAVES) void stream_kernel(StreamArgs g) {
         const uint32_t page = at_slot / SY_PAGE, in_page = at_slot % SY_PAGE;
         const int head = col / g.hd, dim = col % g.hd;
         if (head < g.Hq + g.Hkv) {
-          const float r0 = v[0] * ahead[0] - v[1] * ahead[1], r1 = v[0] * ahead[1] + v[1] * ahead[0];
-          const float r2 = v[2] * ahead[2] - v[3] * ahead[3], r3 = v[2] * ahead[3] + v[3] * ahead[2];
+          float r0, r1, r2, r3;
+          rotate_pair(v[0], v[1], ahead[0], ahead[1], r0, r1);
+          rotate_pair(v[2], v[3], ahead[2], ahead[3], r2, r3);
           const uint32_t p0 = pack_bf2(r0, r1), p1 = pack_bf2(r2, r3);
           if (head < g.Hq) {
             const size_t to = ((size_t)l16 * g.Hq + head) * g.hd + dim;

@@ -185,6 +185,70 @@ def test_kv_append_takes_rows_and_pools_that_start_four_bytes_off():
     ver.close()
 
 
+@pytest.mark.parametrize("slices", range(1, 9))
+@pytest.mark.parametrize("T,tile", [(5, -1), (16, -1), (29, 101)], ids=["stream8", "stream16", "tile"])
+def test_rotary_pairs_round_in_the_pinned_order(T, tile, slices):
+    """r0 = fma(v0, c, -(v1 s)), r1 = fma(v1, c, v0 s) for both kernels that rotate, bit for bit.  Rows of +-1 (RMS exactly 1)
+    and one weight per output make every projected value exact, so q's bf16 (hi, lo) pair and the cached K and V are known to
+    the last bit; float64 holds each product and, but for one sum in 2^29, what the fused operation rounds."""
+    synera = _synera()
+    hd, Hq, Hkv, d = 64, 4, 2, 256 * slices
+    shape = wl.ModelShape("rotary", 1, d, Hq, Hkv, hd, 128, 128, rms_eps=0.0)
+    rng = np.random.default_rng(100 * slices + T)
+    signs = rng.choice([-1.0, 1.0], (128, d)).astype(np.float32)
+
+    def bf16(a):
+        return torch.from_numpy(np.ascontiguousarray(a)).to(DEV).to(torch.bfloat16)
+
+    head = {"embed": bf16(signs), "final_norm": torch.ones(d, dtype=torch.bfloat16, device=DEV), "lm_head": bf16(signs)}
+    lw = wl.draw_layer_weights(shape, 5, 0, DEV)
+    pick, value = {}, {}
+    for name, n in (("wq", Hq * hd), ("wk", Hkv * hd), ("wv", Hkv * hd)):
+        pick[name] = rng.integers(0, d, n)
+        value[name] = bf16(rng.uniform(0.25, 4.0, n).astype(np.float32)).float().cpu().numpy()
+        w = np.zeros((n, d), np.float32)
+        w[np.arange(n), pick[name]] = value[name]
+        lw[name] = bf16(w)
+    lw["attn_norm"] = torch.ones(d, dtype=torch.bfloat16, device=DEV)
+    ctx, pages = 1003, 65
+    toks = rng.integers(0, 128, T).astype(np.int32)
+    ver = synera.Verifier(shape, head, [lw], max_batch=1, max_tokens=T, max_pages=pages)
+    kp = torch.zeros((1, pages, Hkv, wl.PAGE_SIZE, hd), dtype=torch.bfloat16, device=DEV)
+    vp = torch.zeros((1, pages, Hkv, hd, wl.PAGE_SIZE), dtype=torch.bfloat16, device=DEV)
+    bt = np.arange(pages, dtype=np.int32).reshape(1, pages)
+    synera.debug_set_gemm_tile(tile)
+    try:
+        if tile >= 0:      # K = 256 s is cut into s slices, which the rotary kernel adds
+            assert synera.debug_gemm_plan(T, (Hq + 2 * Hkv) * hd, d, 0, True)[2] == slices
+        ver.verify(np.array([ctx], np.int32), np.array([0], np.int32), np.array([T], np.int32), torch.from_numpy(toks).to(DEV),
+                   torch.zeros(1, dtype=torch.int32, device=DEV), bt, pages, kp, vp)
+        q = [ver.debug_read_scratch(w, torch.empty((T, Hq * hd), dtype=torch.bfloat16, device=DEV)) for w in (1, 2)]
+        torch.cuda.synchronize()
+    finally:
+        synera.debug_set_gemm_tile(-1)
+    ver.close()
+    ang = (ctx + np.arange(T, dtype=np.float64))[:, None] * np.power(10000.0, -np.arange(hd // 2) / (hd // 2))
+    c, s = np.cos(ang).astype(np.float32)[:, None], np.sin(ang).astype(np.float32)[:, None]
+
+    def rotated(name, heads):
+        v = (signs[toks][:, pick[name]] * value[name]).reshape(T, heads, hd // 2, 2)
+        v0, v1 = v[..., 0], v[..., 1]
+        out = np.empty((T, heads, hd // 2, 2), np.float32)
+        out[..., 0] = v0.astype(np.float64) * c - v1 * s               # the float32 product is the one rounded first
+        out[..., 1] = v1.astype(np.float64) * c + v0 * s
+        return torch.from_numpy(out.reshape(T, heads * hd))
+
+    want = rotated("wq", Hq)
+    hi = want.to(torch.bfloat16)
+    assert torch.equal(q[0].cpu(), hi)
+    assert torch.equal(q[1].cpu(), (want - hi.float()).to(torch.bfloat16))
+    at = torch.arange(ctx, ctx + T, device=DEV)
+    got_k = kp[0, at // 16, :, at % 16].reshape(T, Hkv * hd).cpu()
+    got_v = vp[0, at // 16, :, :, at % 16].reshape(T, Hkv * hd).cpu()
+    assert torch.equal(got_k, rotated("wk", Hkv).to(torch.bfloat16))
+    assert torch.equal(got_v, torch.from_numpy(signs[toks][:, pick["wv"]] * value["wv"]).to(torch.bfloat16))
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 128, 64), (16, 256, 256), (130, 384, 512), (128, 4096, 4096),
                                    (544, 1024, 14336), (257, 32000, 256)])
 def test_gemm_matches_float64(M, N, K):
