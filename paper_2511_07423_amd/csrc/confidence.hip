@@ -133,8 +133,10 @@ __global__ __launch_bounds__(256) void confidence_kernel(const void* __restrict_
 // Afterwards the k-th largest of the 512 thread maxima is a lower bound of the k-th largest logit, and a tight one:
 // of independent logits about 1.4 k at k = 256, k + few for small k, are not below it.  Only the groups whose maximum reaches the bound are read again (from L2), their
 // entries that reach it are collected in LDS, and each finds its rank by comparing with all others: ranks below k
-// are the answer, in order.  Rows that put more than TOPK_CAP entries at or above the bound (plateaus of ties, masked
-// vocabularies) take an exact radix search over (logit, id) instead, which ends with k entries.
+// are the answer, in order.  Masked vocabularies (fewer finite thread maxima than the list is long) and plateaus of ties (more
+// than TOPK_CAP entries at or above the bound) have few entries above one logit that very many hold: the list is filled up with its
+// holders of the lowest ids, found by walking the row from its start.  Any other row with more than TOPK_CAP such entries takes an
+// exact radix search over (logit, id), which ends with k entries.
 // Bound by the one read of the row: 532 x 32000 f32, k = 160: 439 us with sorted lists kept across the lanes of
 // each wavefront (an insertion per new entry), 26 us.
 #define TOPK_WIDE_MAX 256
@@ -224,7 +226,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void confidence_topk_kernel(const voi
   const RowReader<BF16> rd(logits, row, vocab, stride);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int want = max(k, 2);                        // the margin needs the two best whatever k is
-  // group j of this thread: loads (j per + g) 1024 + tid, g < per
+  // group j of this thread: loads (j per + g) TOPK_THREADS + tid, g < per
   const int per = MULTI ? (rd.n_vec + NV * TOPK_THREADS - 1) / (NV * TOPK_THREADS) : 1;
 
   // ---- the row streams by
@@ -305,34 +307,117 @@ __global__ __launch_bounds__(TOPK_THREADS) void confidence_topk_kernel(const voi
   bound = max(bound, 1u);                            // fewer than want threads saw anything: every comparable entry
 
   // ---- collect what reaches the bound
+  constexpr uint32_t MASKED = 0x007FFFFFu;           // list_key(-inf)
+  uint32_t tie = bound <= MASKED ? MASKED : 0u;      // the logit whose holders fill the list up (block-uniform)
   auto composite = [](uint32_t key, int id) { return ((unsigned long long)key << 32) | (0xFFFFFFFFu - (uint32_t)id); };
   auto push = [&](unsigned long long c) {
     const int at = atomicAdd(&n_list, 1);
     if (at < TOPK_CAP) list[at] = c;
   };
-  {
+  // Every entry of the groups that reach `from`, until the list is full.  (The maxima are compared as floats: four blocks to a
+  // compute unit leave no registers for their keys as well.)
+  auto collect = [&](float from, auto&& take) {
     uint32_t hit = 0;
 #pragma unroll
-    for (int j = 0; j < NV; ++j) hit |= list_key(gmax[j]) >= bound ? 1u << j : 0u;
+    for (int j = 0; j < NV; ++j) hit |= gmax[j] >= from ? 1u << j : 0u;
     while (hit) {                                    // lanes take their groups side by side
       const int j = __builtin_ctz(hit);
       hit &= hit - 1;
+      if (*(volatile int*)&n_list > TOPK_CAP) break;
       for (int g = 0; g < per; ++g) {
         const int c = (j * per + g) * TOPK_THREADS + tid;
         if (c >= rd.n_vec) break;
         float v[VEC];
         RowReader<BF16>::unpack(rd.raw(c), v);
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-          const uint32_t key = list_key(v[i]);
-          if (key >= bound) push(composite(key, c * VEC + i));
-        }
+        for (int i = 0; i < VEC; ++i) take(list_key(v[i]), c * VEC + i);
       }
     }
-    if (tail_key >= bound) push(composite(tail_key, rd.n_vec * VEC + tid));
+    if (tid < rd.n_tail) take(tail_key, rd.n_vec * VEC + tid);
+  };
+  {
+    const uint32_t least = tie ? MASKED + 1u : bound;
+    collect(key_value(least), [&](uint32_t key, int id) {
+      if (key >= least) push(composite(key, id));
+    });
   }
   __syncthreads();
   int n = n_list;
+  if (n > TOPK_CAP && !tie) {                        // block-uniform
+    // ---- a plateau at the bound?  The bound has 24 bits; groups above all logits that share them are few.  If the largest of those
+    // logits is the maximum of enough groups, its holders fill the list up (nothing else is read again).
+    __shared__ uint32_t sh_top;
+    __shared__ int sh_groups;
+    __syncthreads();                                 // n_list is read
+    if (tid == 0) {
+      n_list = 0;
+      sh_top = 0;
+      sh_groups = 0;
+    }
+    __syncthreads();
+    const uint32_t last = bound | 0xFFu;
+    const float least = key_value(bound), above = key_value(last + 1u);   // (beyond +inf: NaN, which nothing reaches)
+    uint32_t top = tail_key >= bound && tail_key <= last ? tail_key : 0u;
+    float gtop = __uint_as_float(0x7FC00000u);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) gtop = fmaxf(gtop, gmax[j] >= least && !(gmax[j] >= above) ? gmax[j] : gtop);
+    top = max(top, list_key(gtop));
+    collect(above, [&](uint32_t key, int id) {
+      if (key > last) push(composite(key, id));
+      else if (key >= bound) top = max(top, key);
+    });
+    for (int o = 32; o > 0; o >>= 1) top = max(top, (uint32_t)__shfl_xor(top, o));
+    if (lane == 0) atomicMax(&sh_top, top);
+    __syncthreads();
+    top = sh_top;
+    gtop = key_value(top);
+    int groups = tail_key == top ? 1 : 0;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) groups += gmax[j] == gtop ? 1 : 0;
+    for (int o = 32; o > 0; o >>= 1) groups += __shfl_xor(groups, o);
+    if (lane == 0) atomicAdd(&sh_groups, groups);
+    __syncthreads();
+    if (n_list < want && n_list + sh_groups >= want) {   // block-uniform
+      n = n_list;
+      tie = top;
+    }
+  }
+  if (tie && n < want) {                             // block-uniform
+    // ---- the holders of `tie` with the lowest ids: VEC entries per thread and round, in id order
+    const int need = want - n;
+    int found = 0, buf = 0;
+    for (int c0 = 0; c0 <= rd.n_vec && found < need; c0 += TOPK_THREADS) {
+      const int c = c0 + tid;
+      float v[VEC];
+      RowReader<BF16>::unpack(rd.n_vec > 0 ? rd.raw(min(c, rd.n_vec - 1)) : make_uint4(0u, 0u, 0u, 0u), v);
+      int before = 0, all = 0;                       // holders in the lanes below, in the wavefront
+      unsigned long long mask[VEC];
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) {
+        const float x = c < rd.n_vec ? v[i] : (c == rd.n_vec && i < rd.n_tail ? rd.tail(i) : __uint_as_float(0x7FC00000u));
+        mask[i] = __builtin_amdgcn_ballot_w64(list_key(x) == tie);
+        before += __builtin_popcountll(mask[i] & ((1ull << lane) - 1));
+        all += __builtin_popcountll(mask[i]);
+      }
+      if (lane == 0) cnts[buf][wave] = all;
+      __syncthreads();
+      int at = n + found + before;
+#pragma unroll
+      for (int w = 0; w < TOPK_THREADS / 64; ++w) {
+        at += w < wave ? cnts[buf][w] : 0;
+        found += cnts[buf][w];
+      }
+#pragma unroll
+      for (int i = 0; i < VEC; ++i)
+        if (mask[i] >> lane & 1) {
+          if (at < want) list[at] = composite(tie, c * VEC + i);
+          ++at;
+        }
+      buf ^= 1;
+    }
+    __syncthreads();
+    n = min(n + found, want);
+  }
   if (n > TOPK_CAP) {                                // block-uniform
     // ---- exact search: (key, ~id) digit by digit, 8 bits per pass over the row
     uint32_t* bins = keys;                           // 256 counters

@@ -62,6 +62,48 @@ def test_topk_ties_plateaus_and_degenerate_rows():
         _check_topk(y, k, f"bf16 ties k={k}")
 
 
+def _masked_rows(vocab, dtype):
+    """Rows with few comparable or few distinct entries, each paths of its own through the list kernel."""
+    g = torch.Generator(device=DEV).manual_seed(vocab)
+    pitch = (vocab + 7) // 8 * 8
+    ids = torch.arange(vocab, device=DEV)
+    x = (torch.randn((10, pitch), generator=g, device=DEV) * 3).to(dtype)[:, :vocab]
+    r, inf = x.clone(), float("inf")
+    x[0] = -inf
+    x[1] = -inf; x[1, vocab // 2] = 1.0
+    x[2] = -inf; x[2, 5::vocab // 50] = r[2, 5::vocab // 50]                 # about 50 live tokens
+    x[3] = torch.finfo(dtype).min; x[3, 3::vocab // 40] = r[3, 3::vocab // 40]
+    x[4] = float("nan"); x[4, 7:12] = r[4, 7:12]; x[4, vocab - 1] = -inf     # six comparable entries
+    x[5] = -inf; x[5, [0, 3]] = 2.0; x[5, 5] = float("nan")                  # the last entries needed lie in the ragged tail
+    x[6] = -1.5                                                              # one plateau
+    x[7] = 0.0; x[7, ::97] = r[7, ::97].abs() + 1                            # a plateau below some larger entries
+    x[8] = (1.0 + (ids * 37 % 128) * 2.0 ** -23).to(dtype)                   # f32: a crowd of logits that share 24 bits
+    x[9] = 0.0; few = ids // (16 // x.element_size()) % 512 < 10             # f32, bf16: large entries in ten threads' loads alone
+    x[9, few] = r[9, few].abs() + 1
+    return x
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("vocab", [257, 1037, 32000, 128256])
+def test_topk_of_masked_rows_and_plateaus(dtype, vocab):
+    synera = _synera()
+    x = _masked_rows(vocab, dtype)
+    h = x.float().cpu().numpy().astype(np.float64)
+    for k in (1, 8, 64, 256):
+        ids, pr, mg, _ = (t.cpu().numpy() for t in synera.confidence_topk(x, k))
+        for r in range(x.shape[0]):
+            live = np.nonzero(~np.isnan(h[r]))[0]
+            order = live[np.lexsort((live, -h[r, live]))]
+            n = min(k, len(order))
+            assert np.array_equal(ids[r, :n], order[:n]) and (ids[r, n:] == 0).all(), (r, k)
+            if r == 0:
+                continue                                                     # no probability to speak of
+            p = np.exp(h[r, order] - h[r, order[0]])
+            p = np.append(p / p.sum(), 0.0)
+            assert np.all(np.abs(pr[r, :n] - p[:n]) <= 1e-4 * p[:n] + 1e-12) and (pr[r, n:] == 0).all(), (r, k)
+            assert abs(mg[r] - (p[0] - p[1])) <= 1e-4, (r, k)
+
+
 def test_topk_first_entry_equals_plain_confidence_and_errors():
     synera = _synera()
     x = wl.draw_confidence_logits(64, shapes.C5B_VOCAB, shapes.C5B_STD, shapes.C5B_BOOST_HI, 77, DEV, torch.bfloat16)
