@@ -353,7 +353,7 @@ struct Plan {
   int32_t T, R, R_all;      // chunk tokens, draft rows, LM-head rows (drafts + last-uncached rows)
   const int32_t *d_cu_keys, *d_imp_items;   // importance-score blocks: prefix sums of L_i + chunk_i; (request, first key)
   int32_t n_imp_items, total_keys;
-  const int32_t* d_cu_win;  // append only: prefix sums of the pages each request's rows touch
+  const int32_t* d_cu_win;  // append by page tiles only: prefix sums of the pages each request's rows touch
   int32_t n_win;
   int slot;
 };
@@ -566,7 +566,9 @@ static int32_t build_plan(synera_ctx* c, int32_t B, const int32_t* ctx_len, cons
     p.d_cuts = reinterpret_cast<const AttnCut*>(d + o_cuts);
     at = o_prog + n_pos * 4;
   }
-  if (!with_attention) {
+  p.d_cu_win = nullptr;
+  p.n_win = 0;
+  if (!with_attention && !kv_append_by_rows(T, c->desc.n_kv_heads * c->desc.head_dim)) {
     const size_t o_win = region((size_t)B + 1);
     int32_t n_win = 0;
     for (int i = 0; i < B; ++i) {
@@ -1096,7 +1098,7 @@ extern "C" int32_t synera_kv_append(synera_ctx* c, int32_t layer, int32_t B, con
   const size_t layer_elems = (size_t)n_pages_in_pool * Hkv * SY_PAGE * hd;
   const hipError_t e = launch_kv_append(static_cast<const bf16_t*>(d_k), static_cast<const bf16_t*>(d_v), p.meta, p.d_cu_win,
                                         p.n_win, B, static_cast<bf16_t*>(d_k_pool) + (size_t)layer * layer_elems,
-                                        static_cast<bf16_t*>(d_v_pool) + (size_t)layer * layer_elems, Hkv, hd, s);
+                                        static_cast<bf16_t*>(d_v_pool) + (size_t)layer * layer_elems, p.T, Hkv, hd, s);
   if (e != hipSuccess) (void)hipGetLastError();
   const int32_t fin = finish_call(c, p, s);      // the upload is queued either way: the slot is busy
   return e != hipSuccess ? SYNERA_EHIP : fin;

@@ -76,9 +76,11 @@ hipError_t launch_rmsnorm(float* x, const float* parts, int n_parts, size_t part
 hipError_t launch_rope_append(const float* qkv, int n_parts, size_t part_stride, const float2* cs, const BatchMeta& m,
                               bf16_t* q_hi, bf16_t* q_lo, bf16_t* k_layer, bf16_t* v_layer, int T, int Hq, int Hkv,
                               int hd, bool lo_off, hipStream_t s);
-// cu_win: device [B+1], prefix sums of the pages each request's new rows touch (n_win in all).
+// T rows in all of n = Hkv hd values.  cu_win: device [B+1], prefix sums of the pages each request's new rows touch (n_win in
+// all); null where the rows go one by one.
+bool kv_append_by_rows(int64_t T, int n);
 hipError_t launch_kv_append(const bf16_t* k, const bf16_t* v, const BatchMeta& m, const int32_t* cu_win, int n_win, int B,
-                            bf16_t* k_layer, bf16_t* v_layer, int Hkv, int hd, hipStream_t s);
+                            bf16_t* k_layer, bf16_t* v_layer, int T, int Hkv, int hd, hipStream_t s);
 hipError_t launch_accept(const int32_t* tokens, const int32_t* anchor, const int32_t* lm_argmax, const BatchMeta& m,
                          int B, int R, int32_t* out_argmax, int32_t* accept_len, int32_t* correction,
                          hipStream_t s);

@@ -264,15 +264,42 @@ hipError_t launch_rope_append(const float* qkv, int n_parts, size_t part_stride,
 }
 
 // ------------------------------------------------------------------ standalone append
-// Rows are bf16 already; a pure scatter.  A wavefront owns 128 of a token's n = Hkv hd values for one page, i.e. up to
+// Rows are bf16 already; a pure scatter, by one of two kernels.  The owner of a row (a page window) is found by binary
+// search in prefix sums, so any number of rows per request is allowed.
+//
+// Small calls: a block per row, the shortest way from the lengths to the stores.
+__global__ __launch_bounds__(128) void kv_append_rows_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+                                                             BatchMeta m, int B, bf16_t* __restrict__ k_layer,
+                                                             bf16_t* __restrict__ v_layer, int n, int hd) {
+  const int t = blockIdx.x;
+  int lo = 0, hi = B;                       // find r with cu_tok[r] <= t < cu_tok[r+1]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (m.cu_tok[mid] <= t) lo = mid; else hi = mid;
+  }
+  const int r = lo;
+  const int pos = m.ctx_len[r] + (t - m.cu_tok[r]);
+  const size_t page_at = (size_t)m.block_table[(size_t)r * m.max_pages + pos / SY_PAGE] * n * SY_PAGE;
+  const int slot = pos % SY_PAGE;
+  for (int e = threadIdx.x * 2; e < n; e += 128 * 2) {
+    *reinterpret_cast<uint32_t*>(k_layer + page_at + ((size_t)(e / hd) * SY_PAGE + slot) * hd + e % hd) =
+        *reinterpret_cast<const uint32_t*>(k + (size_t)t * n + e);
+    const uint32_t vv = *reinterpret_cast<const uint32_t*>(v + (size_t)t * n + e);
+    bf16_t* dst = v_layer + page_at + (size_t)e * SY_PAGE + slot;
+    dst[0] = (bf16_t)(vv & 0xFFFF);
+    dst[SY_PAGE] = (bf16_t)(vv >> 16);
+  }
+}
+
+// Large calls: page tiles.  A wavefront owns 128 of a token's n = Hkv hd values for one page, i.e. up to
 // 16 consecutive tokens: its K rows move in 16-byte pieces, its V values (two dims per lane, one load per token) are
 // turned by LDS from token-major to the page's [dim][slot] order, so that both the K and the V tile of a whole page
 // leave as contiguous 4 KB.  The first and the last page of a request may be shared with tokens that are not in this
-// call: there only the covered slots are written, V two bytes at a time.  n is a multiple of 128 (synera_create).
-// Bound by HBM: 24 requests, 28 K tokens, 231 MB read and written: 207 us with one block per token and 2-byte V
-// stores, 59 us.
-// The owner of page window w is found by binary search in the prefix sums, so any number of rows per request is
-// allowed.
+// call: there only the covered slots are written, V by the pair where both slots of a word are covered.  n is a multiple of 128
+// (synera_create).
+// Bound by HBM: 24 requests, 28 K tokens, 231 MB read and written: 207 us with one block per row, 57 us.  64 requests of
+// 50 .. 100 rows, nearly half of whose pages are shared, the whole call with its wait: 55 us with a block per row, 43 with
+// loads guarded by slot and 2-byte V stores in shared pages, 34.
 __global__ __launch_bounds__(256) void kv_append_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
                                                         BatchMeta m, const int32_t* __restrict__ cu_win, int B,
                                                         bf16_t* __restrict__ k_layer, bf16_t* __restrict__ v_layer,
@@ -290,24 +317,17 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const bf16_t* __restrict
   const int r = lo;
   const int L = m.ctx_len[r], t0 = m.cu_tok[r], c = m.cu_tok[r + 1] - t0;
   const int page_pos = (L / SY_PAGE + win - cu_win[r]) * SY_PAGE;       // first position of the page
-  const int s0 = max(L, page_pos) - page_pos, s1 = min(L + c, page_pos + SY_PAGE) - page_pos;   // covered slots
+  const int s0 = max(L, page_pos) - page_pos, s1 = min(L + c, page_pos + SY_PAGE) - page_pos;   // covered slots, at least one
   const size_t page_at = (size_t)m.block_table[(size_t)r * m.max_pages + page_pos / SY_PAGE] * n * SY_PAGE;
   const size_t first = (size_t)(t0 + page_pos - L);                     // row of slot 0 (may lie before the call's rows)
   u32x4 kr[4];
   uint32_t vr[SY_PAGE];
+  // (slots that are not covered load a covered one's row: without branches all loads are on their way together)
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {             // 4 tokens x 16 pieces per load
-    const int slot = j * 4 + (lane >> 4);
-    if (slot >= s0 && slot < s1) kr[j] = *reinterpret_cast<const u32x4*>(k + (first + slot) * n + e0 + (lane & 15) * 8);
-  }
-  if (s0 == 0 && s1 == SY_PAGE) {           // wavefront-uniform
+  for (int j = 0; j < 4; ++j)               // 4 tokens x 16 pieces per load
+    kr[j] = *reinterpret_cast<const u32x4*>(k + (first + min(max(j * 4 + (lane >> 4), s0), s1 - 1)) * n + e0 + (lane & 15) * 8);
 #pragma unroll
-    for (int j = 0; j < SY_PAGE; ++j) vr[j] = *reinterpret_cast<const uint32_t*>(v + (first + j) * n + e0 + 2 * lane);
-  } else {
-#pragma unroll
-    for (int j = 0; j < SY_PAGE; ++j)
-      if (j >= s0 && j < s1) vr[j] = *reinterpret_cast<const uint32_t*>(v + (first + j) * n + e0 + 2 * lane);
-  }
+  for (int j = 0; j < SY_PAGE; ++j) vr[j] = *reinterpret_cast<const uint32_t*>(v + (first + min(max(j, s0), s1 - 1)) * n + e0 + 2 * lane);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int slot = j * 4 + (lane >> 4), e = e0 + (lane & 15) * 8;
@@ -315,42 +335,53 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const bf16_t* __restrict
       *reinterpret_cast<u32x4*>(k_layer + page_at + ((size_t)(e / hd) * SY_PAGE + slot) * hd + e % hd) = kr[j];
   }
   bf16_t* dst = v_layer + page_at + (size_t)e0 * SY_PAGE;               // 128 dims x 16 slots
-  if (s0 == 0 && s1 == SY_PAGE) {
-    // lane's two rows of 16 slots = 16 words; the pieces of 4 words rotate with the lane so that the 16-byte LDS
-    // accesses of neighbouring lanes fall on different banks
-    uint32_t* mine = turn[wave] + lane * 16;
+  // lane's two rows of 16 slots = 16 words; the pieces of 4 words rotate with the lane so that the 16-byte LDS
+  // accesses of neighbouring lanes fall on different banks
+  uint32_t* mine = turn[wave] + lane * 16;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {           // piece q: slots (q & 1) * 8 .. + 7 of dim q >> 1
-      u32x4 w;
+  for (int q = 0; q < 4; ++q) {             // piece q: slots (q & 1) * 8 .. + 7 of dim q >> 1
+    u32x4 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t a = vr[(q & 1) * 8 + 2 * i], b = vr[(q & 1) * 8 + 2 * i + 1];
+      w[i] = (q >> 1) ? (a >> 16) | (b & 0xFFFF0000u) : (a & 0xFFFFu) | (b << 16);
+    }
+    *reinterpret_cast<u32x4*>(mine + ((q + (lane >> 1)) & 3) * 4) = w;
+  }
+  __builtin_amdgcn_wave_barrier();
+  const bool whole = s0 == 0 && s1 == SY_PAGE;                          // wavefront-uniform
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int piece = j * 64 + lane, from = piece >> 2;
+    const u32x4 w = *reinterpret_cast<const u32x4*>(turn[wave] + from * 16 + (((piece & 3) + (from >> 1)) & 3) * 4);
+    const int slot0 = (piece & 1) * 8;                                  // the piece's first slot
+    bf16_t* to = dst + piece * 8;
+    if (whole || (slot0 >= s0 && slot0 + 8 <= s1)) {
+      *reinterpret_cast<u32x4*>(to) = w;
+    } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const uint32_t a = vr[(q & 1) * 8 + 2 * i], b = vr[(q & 1) * 8 + 2 * i + 1];
-        w[i] = (q >> 1) ? (a >> 16) | (b & 0xFFFF0000u) : (a & 0xFFFFu) | (b << 16);
+        const bool a = slot0 + 2 * i >= s0 && slot0 + 2 * i < s1, b = slot0 + 2 * i + 1 >= s0 && slot0 + 2 * i + 1 < s1;
+        if (a && b) *reinterpret_cast<uint32_t*>(to + 2 * i) = w[i];
+        else if (a) to[2 * i] = (bf16_t)(w[i] & 0xFFFF);
+        else if (b) to[2 * i + 1] = (bf16_t)(w[i] >> 16);
       }
-      *reinterpret_cast<u32x4*>(mine + ((q + (lane >> 1)) & 3) * 4) = w;
     }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int piece = j * 64 + lane, from = piece >> 2;
-      const u32x4 w = *reinterpret_cast<const u32x4*>(turn[wave] + from * 16 + (((piece & 3) + (from >> 1)) & 3) * 4);
-      *reinterpret_cast<u32x4*>(dst + piece * 8) = w;
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < SY_PAGE; ++j)
-      if (j >= s0 && j < s1) {
-        dst[(2 * lane) * SY_PAGE + j] = (bf16_t)(vr[j] & 0xFFFF);
-        dst[(2 * lane + 1) * SY_PAGE + j] = (bf16_t)(vr[j] >> 16);
-      }
   }
 }
 
+// The line between them (kv_append_by_rows): the call with its wait, 8B shape (n = 1024): 100 rows 25 us by rows, 27 by tiles; 300 rows 27.0, 27.5; 700
+// rows 31, 30; 830 rows of 64 requests 33, 31.  n = 256: 1100 rows 26, 27; 1900 rows 31, 30; 3000 rows 30, 27.
+bool kv_append_by_rows(int64_t T, int n) { return T * n <= 1 << 19; }
+
 hipError_t launch_kv_append(const bf16_t* k, const bf16_t* v, const BatchMeta& m, const int32_t* cu_win, int n_win, int B,
-                            bf16_t* k_layer, bf16_t* v_layer, int Hkv, int hd, hipStream_t s) {
-  if (n_win <= 0) return hipSuccess;
+                            bf16_t* k_layer, bf16_t* v_layer, int T, int Hkv, int hd, hipStream_t s) {
+  if (T <= 0) return hipSuccess;
   const int n = Hkv * hd;
-  kv_append_kernel<<<dim3(n_win, (n + 511) / 512), 256, 0, s>>>(k, v, m, cu_win, B, k_layer, v_layer, n, hd);
+  if (!cu_win)
+    kv_append_rows_kernel<<<T, 128, 0, s>>>(k, v, m, B, k_layer, v_layer, n, hd);
+  else
+    kv_append_kernel<<<dim3(n_win, (n + 511) / 512), 256, 0, s>>>(k, v, m, cu_win, B, k_layer, v_layer, n, hd);
   return hipGetLastError();
 }
 

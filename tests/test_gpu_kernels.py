@@ -185,6 +185,44 @@ def test_kv_append_takes_rows_and_pools_that_start_four_bytes_off():
     ver.close()
 
 
+@pytest.mark.parametrize("off", [0, 2], ids=["aligned", "4bytes"])
+@pytest.mark.parametrize("n_new", [[2048], [2049], [7] * 292, [7] * 293, [1, 15, 16, 17, 2100, 9]],
+                         ids=["rows", "tiles", "short_rows", "short_tiles", "mixed"])
+def test_kv_append_by_rows_and_by_tiles(n_new, off):
+    """256 values a row: up to 2048 rows go one by one, more by page tiles; one long request, and many short ones most of
+    whose pages are shared with slots that must stay as they are."""
+    synera = _synera()
+    shape = wl.ModelShape("append", 1, 256, 4, 4, 64, 256, 256)
+    head = wl.draw_head_weights(shape, 9, DEV)
+    layers = [wl.draw_layer_weights(shape, 9, 0, DEV)]
+    rng = np.random.default_rng(sum(n_new) + len(n_new))
+    n_new, B = np.array(n_new, np.int32), len(n_new)
+    start = rng.integers(0, 40, B).astype(np.int32)
+    pages = int((start + n_new + 15).max()) // 16
+    bt = rng.permutation(B * pages).astype(np.int32).reshape(B, pages)
+    T = int(n_new.sum())
+    ver = synera.Verifier(shape, head, layers, max_batch=B, max_tokens=64, max_pages=pages)
+
+    def placed(t):                               # the same values `off` elements into a buffer
+        flat = torch.zeros(t.numel() + 8, dtype=torch.bfloat16, device=DEV)
+        flat[off: off + t.numel()] = t.reshape(-1)
+        return flat[off: off + t.numel()].view(t.shape)
+
+    k, v = (placed(wl.draw_normal_bf16((T, 4, 64), 1.0, s, DEV)) for s in (7, 8))
+    kp = placed(torch.full((1, B * pages, 4, 16, 64), 3.0, dtype=torch.bfloat16, device=DEV))
+    vp = placed(torch.full((1, B * pages, 4, 64, 16), 5.0, dtype=torch.bfloat16, device=DEV))
+    want_k, want_v = kp.clone(), vp.clone()
+    pos = np.concatenate([np.arange(s, s + n) for s, n in zip(start, n_new)])
+    page = torch.from_numpy(bt[np.repeat(np.arange(B), n_new), pos // 16].astype(np.int64)).to(DEV)
+    slot = torch.from_numpy(pos % 16).to(DEV)
+    want_k[0, page, :, slot] = k
+    want_v[0, page, :, :, slot] = v
+    ver.kv_append(0, start, n_new, k, v, bt, B * pages, kp, vp)
+    torch.cuda.synchronize()
+    ver.close()
+    assert torch.equal(kp, want_k) and torch.equal(vp, want_v)
+
+
 @pytest.mark.parametrize("slices", range(1, 9))
 @pytest.mark.parametrize("T,tile", [(5, -1), (16, -1), (29, 101)], ids=["stream8", "stream16", "tile"])
 def test_rotary_pairs_round_in_the_pinned_order(T, tile, slices):
