@@ -484,7 +484,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void confidence_topk_kernel(const voi
   }
 
   // ---- ranks
-  const float m = all.m, inv_z = 1.0f / all.Z;
+  const float m = all.m, Z = all.Z;
   for (int at = tid; at < n; at += TOPK_THREADS) {
     const unsigned long long mine = list[at];
     int rank = 0, e = 0;
@@ -493,7 +493,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void confidence_topk_kernel(const voi
       rank += (two.x > mine) + (two.y > mine);
     }
     if (e < n) rank += list[e] > mine;
-    const float pr = fast_exp2((key_value((uint32_t)(mine >> 32)) - m) * LOG2E) * inv_z;
+    const float pr = fast_exp2((key_value((uint32_t)(mine >> 32)) - m) * LOG2E) / Z;   // (divided: one rounding)
     if (rank < k) {
       ids[row * k + rank] = (int32_t)(0xFFFFFFFFu - (uint32_t)mine);
       probs[row * k + rank] = pr;
