@@ -1,6 +1,8 @@
 """GPU parity of the richer vocabulary reduction (top-k compressed distribution, margin score) and of the
 chunk dispatch probability against the CPU oracle, through the C ABI.  Ids bit-exact; probabilities
 1e-4 relative, entropy 1e-3 relative (the standalone confidence tolerances), margin 1e-4 absolute."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -259,6 +261,28 @@ def test_nucleus_of_rows_without_mass(dtype, vocab):
             p = torch.softmax(x[0::2].double(), 1).max(1).values
             assert torch.allclose(mass[0::2].double(), p, rtol=1e-5, atol=0)
     _check_nucleus(x[0:9:2], 0.9, "ordinary rows")
+
+
+def test_nucleus_counts_of_a_vocabulary_too_long_for_the_packed_bins():
+    """2^22 tokens: a bin's count no longer fits beside its mass.  Sums of ones are exact in float32, so the counts of flat and
+    one-hot rows follow from the definition.  Two plateaus: each thread adds 2^14 terms, at most half an ulp off each, so the
+    row's sum is within 2^14 2^-25 = 5e-4 of itself and a count within 0.9 V / (1 + 1 / e) times that of the exact one, 1e-3 V."""
+    synera = _synera()
+    V = 1 << 22
+    x = torch.zeros((4, V), device=DEV)
+    x[1, ::2] = 1.0                                            # two plateaus: p = e / (1 + e) in the upper one
+    x[2] = -20.0; x[2, 5::40000] = 10.0                        # 105 tokens hold all but 4e-7 of the mass
+    x[3, 7] = 40.0
+    n, mass, cut = (t.cpu() for t in synera.nucleus(x, 0.5))
+    assert int(n[0]) == V // 2 and float(mass[0]) == pytest.approx(0.5, abs=1e-6) and float(cut[0]) == 0.0
+    upper = math.e / (1 + math.e)
+    assert abs(int(n[1]) - 0.5 / upper * (V // 2)) <= 1e-3 * V and float(cut[1]) == 1.0
+    assert int(n[2]) == 53 and float(cut[2]) == 10.0
+    assert int(n[3]) == 1 and float(cut[3]) == 40.0
+    n, mass, cut = (t.cpu() for t in synera.nucleus(x, 0.9))
+    assert abs(int(n[0]) - 0.9 * V) <= 1 and abs(int(n[2]) - 0.9 * 105) <= 1
+    # the lower plateau: V / 2 above it, and of it what is missing
+    assert abs(int(n[1]) - (V // 2 + (0.9 - upper) / (1 - upper) * (V // 2))) <= 1e-3 * V and float(cut[1]) == 0.0
 
 
 def test_nucleus_ties_one_hot_masked_and_uniform_rows():

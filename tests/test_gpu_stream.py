@@ -102,4 +102,10 @@ def test_models_outside_the_kernels_forms_take_the_tile_kernels(d_ffn, shift):
 def test_rotary_kernel_adds_every_number_of_slices(slices):
     """The tile kernels cut K = 256 s into s slices here, and the rotary kernel adds them; the streams have none.  384
     values per token: its last block of threads is half empty."""
+    import paper_2511_07423_amd as synera
+    synera.debug_set_gemm_tile(101)
+    try:
+        assert synera.debug_gemm_plan(12, 384, 256 * slices, 0, True)[2] == slices
+    finally:
+        synera.debug_set_gemm_tile(-1)
     test_small_batch_agrees_with_the_tile_kernels((256 * slices, 2, 2, 64, 128, 128), [(37, 3, 4), (15, 0, 5)])
