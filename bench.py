@@ -53,8 +53,13 @@ def plan_fingerprint(synera, shape, b, T):
     import numpy as np
     d, f, V, qkv = shape.d_model, shape.d_ffn, shape.vocab, shape.q_dim + 2 * shape.kv_dim
     parts = []
-    for name, n, k, epi, stored in (("qkv", qkv, d, 0, True), ("o", d, shape.q_dim, 1, True), ("gate_up", 2 * f, d, 2, True),
-                                    ("down", d, f, 1, True), ("lm_head", V, d, 0, False)):
+    # up to 16 tokens no projection is cut into tiles or slices
+    streams = T <= 16 and d <= 8192 and f % 128 == 0
+    if streams:
+        parts.append("projections=streams")
+    projections = (("qkv", qkv, d, 0, True), ("o", d, shape.q_dim, 1, True), ("gate_up", 2 * f, d, 2, True),
+                   ("down", d, f, 1, True), ("lm_head", V, d, 0, False))
+    for name, n, k, epi, stored in () if streams else projections:
         bm, bn, split = synera.debug_gemm_plan(T, n, k, epi, stored)
         # two MFMA K steps per stage, or one with the layers' activation pairs as one array of whole lines
         form = "k64" if synera.debug_gemm_plan_bk(T, n, k, epi, stored) == 64 else ("pair" if stored else "")

@@ -23,7 +23,10 @@ extern "C" {
  * synera_verify calls is bracketed by a HIP event pair on the call's stream.
  * synera_profile_end waits for those events, returns how many launches were
  * bracketed and the sum of their durations in milliseconds, and switches the
- * timing off.  Errors: EINVAL (null, unknown stage), EHIP.
+ * timing off.  Batches of up to 16 tokens (of models whose projections stream: d_ffn a multiple of 128,
+ * d_model <= 8192, RMSNorm gains on 16 bytes) have no launches of their own for NORM and ROPE_APPEND: QKV contains
+ * the norm, the rotary embedding and the append, GATE_UP and LM_HEAD the norm.
+ * Errors: EINVAL (null, unknown stage), EHIP.
  */
 typedef enum synera_stage {
   SYNERA_STAGE_NONE = 0,

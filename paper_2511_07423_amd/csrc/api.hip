@@ -116,7 +116,7 @@ struct synera_ctx {
   struct {
     const int32_t *ctx_len, *cu_tok, *block_table, *cu_keys, *items, *n_unc, *cu_draft;
     BatchMeta meta;
-    int32_t B, T, R, n_items, max_pages, total_keys, n_pages_in_pool, slot;
+    int32_t B, R, n_items, max_pages, total_keys, n_pages_in_pool, slot;
     const void* k_pool;
     bool valid;
     bool all_rows_kept;          // every request had an uncached token: c->logits / lm_ids / lm_p hold all LM-head rows
@@ -918,7 +918,6 @@ extern "C" int32_t synera_verify(synera_ctx* c, int32_t B, const int32_t* h_ctx_
   c->last.cu_keys = p.d_cu_keys;
   c->last.items = p.d_imp_items;
   c->last.B = B;
-  c->last.T = p.T;
   c->last.n_pages_in_pool = n_pages_in_pool;
   c->last.k_pool = d_k_pool;
   c->last.R = p.R;

@@ -534,7 +534,7 @@ hipError_t launch_confidence_topk(const void* logits, int dtype, int64_t rows, i
 //
 // One block of 512 threads per row, four on a compute unit.  After the statistics pass (m, Z) the row is read twice
 // more, from L2 or the last-level cache (kept in registers instead, half as many rows fit a compute unit: 50 against
-// 46 us on 532 rows, 480 against 300 us on 2048 x 128256 bf16).  The cut is found by histogram: 1024 bins of 1/32 in the
+// 46 us on 532 rows, 480 against 344 us on 2048 x 128256 bf16).  The cut is found by histogram: 1024 bins of 1/32 in the
 // logit below the maximum, each with its entries' count and probability mass (one packed LDS atomic per entry; the bins are
 // narrow so that the lanes of a wavefront rarely meet in one).  The bin where the running mass, from the largest
 // logits down, reaches top_p holds a few dozen entries: they are listed and each sums the masses above itself.  A bin

@@ -50,7 +50,7 @@ def confidence():
             print(json.dumps({"kernel": f"synera_confidence_topk (k = {k})", "rows": shapes.C5B_ROWS, "vocab": shapes.C5B_VOCAB,
                               "dtype": name, "bytes": nbytes, "avg_launch_ms": ms, "bound": "hbm",
                               "achieved_GBs": nbytes / ms / 1e6, "peak_GBs": 8000.0, "frac": nbytes / ms / 1e6 / 8000.0}))
-        ms = _time(lambda: synera.nucleus(x, 0.9))            # one read for the maximum and the sum, four for the radix search
+        ms = _time(lambda: synera.nucleus(x, 0.9))            # three reads: maximum and sum, histogram, the cut's bin
         print(json.dumps({"kernel": "synera_nucleus (top_p = 0.9)", "rows": shapes.C5B_ROWS, "vocab": shapes.C5B_VOCAB,
                           "dtype": name, "bytes": nbytes, "avg_launch_ms": ms, "bound": "hbm",
                           "achieved_GBs": nbytes / ms / 1e6, "peak_GBs": 8000.0, "frac": nbytes / ms / 1e6 / 8000.0}))
