@@ -176,10 +176,10 @@ struct RowReader {                                   // a row as 16-byte pieces 
       v[2] = __uint_as_float(raw.z); v[3] = __uint_as_float(raw.w);
     }
   }
-  __device__ __forceinline__ float tail(int e) const {
-    const int64_t at = (int64_t)n_vec * VEC + e;
-    return BF16 ? bf2f(reinterpret_cast<const bf16_t*>(base)[at]) : reinterpret_cast<const float*>(base)[at];
+  __device__ __forceinline__ float at(int64_t e) const {
+    return BF16 ? bf2f(reinterpret_cast<const bf16_t*>(base)[e]) : reinterpret_cast<const float*>(base)[e];
   }
+  __device__ __forceinline__ float tail(int e) const { return at((int64_t)n_vec * VEC + e); }
 };
 
 // The row's statistics from every thread's own, left in *all (LDS); ends with a barrier.
@@ -717,7 +717,7 @@ __global__ __launch_bounds__(NUC_THREADS, 8) void nucleus_kernel(const void* __r
         sh_above = above;
         sh_count_above = count_above;
         sh_bin_mass = 0;
-        sh_bin_count = 0;
+        sh_bin_count = 0xFFFFFFFFu;                  // more than the list holds: looked at where a crowded bin is
       }
       sh_lo = 0xFFFFFFFFu;
       sh_hi = 0;
@@ -742,25 +742,27 @@ __global__ __launch_bounds__(NUC_THREADS, 8) void nucleus_kernel(const void* __r
   };
 
   bool reached = find();
-  if (sh_bin_mass == 0) {                            // block-uniform: a row without mass
-    uint32_t top = 0;
-    each_value([&](float v) { top = max(top, order_key(v)); });
-    for (int o = 32; o > 0; o >>= 1) top = max(top, (uint32_t)__shfl_xor(top, o));
-    if (lane == 0) atomicMax(&sh_hi, top);
-    __syncthreads();
-    top = sh_hi;
-    int holders = 0;
-    each_value([&](float v) { holders += order_key(v) == top ? 1 : 0; });
-    for (int o = 32; o > 0; o >>= 1) holders += __shfl_xor(holders, o);
-    if (lane == 0) atomicAdd(&n_list, holders);
-    __syncthreads();
-    if (tid == 0) finish(top, 0, asked > 0 ? (uint32_t)n_list : 1u, 0, 0);
-    return;
-  }
   uint32_t lo = 0, hi = 0xFFFFFFFFu;                 // keys of the bin's entries, once they have been asked for
   const int bin0 = (int)sh_bin;
   bool by_key = false;                               // membership: by first_bin == bin0, then by lo <= key <= hi
   while (sh_bin_count > NUC_CAP) {                   // block-uniform
+    if (sh_bin_mass == 0) {                          // block-uniform: a row without mass
+      uint32_t top = 0;                                // (one entry per thread and round: few registers, and rare)
+#pragma unroll 1
+      for (int64_t e = tid; e < vocab; e += NUC_THREADS) top = max(top, order_key(rd.at(e)));
+      for (int o = 32; o > 0; o >>= 1) top = max(top, (uint32_t)__shfl_xor(top, o));
+      if (lane == 0) atomicMax(&sh_hi, top);
+      __syncthreads();
+      top = sh_hi;
+      int holders = 0;
+#pragma unroll 1
+      for (int64_t e = tid; e < vocab; e += NUC_THREADS) holders += order_key(rd.at(e)) == top ? 1 : 0;
+      for (int o = 32; o > 0; o >>= 1) holders += __shfl_xor(holders, o);
+      if (lane == 0) atomicAdd(&n_list, holders);
+      __syncthreads();
+      if (tid == 0) finish(top, 0, asked > 0 ? (uint32_t)n_list : 1u, 0, 0);
+      return;
+    }
     uint32_t mn = 0xFFFFFFFFu, mx = 0;
     each_value([&](float v) {
       const uint32_t key = order_key(v);
