@@ -297,7 +297,7 @@ __global__ __launch_bounds__(128) void kv_append_rows_kernel(const bf16_t* __res
 // leave as contiguous 4 KB.  The first and the last page of a request may be shared with tokens that are not in this
 // call: there only the covered slots are written, V by the pair where both slots of a word are covered.  n is a multiple of 128
 // (synera_create).
-// Bound by HBM: 24 requests, 28 K tokens, 231 MB read and written: 207 us with one block per row, 57 us.  64 requests of
+// Bound by HBM: 24 requests, 28 K tokens, 231 MB read and written: 207 us with one block per row, 53 us a call, 36 us of it the kernel.  64 requests of
 // 50 .. 100 rows, nearly half of whose pages are shared, the whole call with its wait: 55 us with a block per row, 43 with
 // loads guarded by slot and 2-byte V stores in shared pages, 34.
 __global__ __launch_bounds__(256) void kv_append_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
