@@ -111,6 +111,7 @@ struct synera_ctx {
   float* part_ml;
   float2* row_ml;              // [max_tokens][Hq] softmax statistics of the last layer's attention rows
   bool streams;                // whether this model's projections fit stream.hip
+  bool weights_once;           // the weights are more than the caches hold from one verify to the next
   int32_t* imp_records;        // synera_importance: one record per item of the batch
   // batch of the last synera_verify, for synera_importance: device pointers into that call's metadata slot
   struct {
@@ -233,6 +234,9 @@ extern "C" int32_t synera_create(synera_ctx** out, const synera_model_desc* desc
   uintptr_t gains = reinterpret_cast<uintptr_t>(w->final_norm);
   for (const synera_layer_weights& lw : c->layers) gains |= reinterpret_cast<uintptr_t>(lw.attn_norm) | reinterpret_cast<uintptr_t>(lw.mlp_norm);
   c->streams = m.d_ffn % 128 == 0 && m.d_model <= SY_STREAM_NORM_WIDTH && (gains & 15) == 0;
+  // 256 MB: the last-level cache.  (A decoder of 7 MB whose weights were marked all the same took 89.7 instead of 88.1 us a verify.)
+  const size_t per_layer = (size_t)m.d_model * (2 * m.n_q_heads * m.head_dim + 2 * m.n_kv_heads * m.head_dim) + 3 * (size_t)m.d_model * m.d_ffn;
+  c->weights_once = 2 * (m.n_layers * per_layer + (size_t)m.vocab * m.d_model) > ((size_t)256 << 20);
   c->max_batch = max_batch;
   c->max_tokens = max_tokens;
   c->max_pages = max_pages;
@@ -353,6 +357,7 @@ struct Plan {
   int32_t T, R, R_all;      // chunk tokens, draft rows, LM-head rows (drafts + last-uncached rows)
   const int32_t *d_cu_keys, *d_imp_items;   // importance-score blocks: prefix sums of L_i + chunk_i; (request, first key)
   int32_t n_imp_items, total_keys;
+  int64_t keys_shared;         // keys that two groups of query rows read
   const int32_t* d_cu_win;  // append by page tiles only: prefix sums of the pages each request's rows touch
   int32_t n_win;
   int slot;
@@ -391,6 +396,7 @@ static int32_t build_plan(synera_ctx* c, int32_t B, const int32_t* ctx_len, cons
   size_t o_pos = 0, o_slot = 0, o_sel = 0;
   int32_t R_all = R;
   p.n_shares = p.n_cuts = 0;
+  p.keys_shared = 0;
   p.d_prog = nullptr;
   p.d_units = nullptr;
   p.d_shares = nullptr;
@@ -449,6 +455,7 @@ static int32_t build_plan(synera_ctx* c, int32_t B, const int32_t* ctx_len, cons
     double iters[2] = {0.0, 0.0};                    // iterations of each class (every stream once per KV head)
     for (int i = 0; i < B; ++i) {
       const int qn = n_unc[i] + n_draft[i];
+      if (qn > tg) p.keys_shared += ctx_len[i] + qn;
       for (int j0 = 0; j0 < qn; j0 += tg) {
         const int ntok = std::min(tg, qn - j0);
         const Stream st{i, h[o_cu + i] + j0, j0, ntok, ctx_len[i] + j0 + ntok};
@@ -730,6 +737,9 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
   al.Hq = Hq;
   al.Hkv = Hkv;
   al.hd = hd;
+  // No cache holds the keys until the next verify (see weights_once), and most of them are read by one block: where chunks of
+  // 18 tokens (72 rows: two groups) made every stream two, a layer took 8 us longer with its keys marked.
+  al.once = (c->weights_once || (size_t)p.total_keys * m.n_layers * kd * 4 > ((size_t)256 << 20)) && 2 * p.keys_shared < p.total_keys;
 
   // Which projections read their activation pair as one paired array (the producer writes it that way then).  The
   // ablation of low parts works on separate arrays: any of its bits keeps them.
@@ -742,6 +752,7 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
   normed.ss = c->ss;
   normed.ss_parts = 1;                       // (the embedding's)
   normed.eps = m.rms_eps;
+  normed.once = added.once = c->weights_once;
   added.ss_out = c->ss;
 
   // K-split projections leave their slices in c->gparts; the kernel that reads the result next adds them

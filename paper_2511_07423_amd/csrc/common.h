@@ -152,6 +152,7 @@ struct AttnLaunch {
   float2* row_ml;            // optional [T][Hq]: per query row the softmax reference m (exponent-2 domain) and
                              // the sum l of 2^(s - m) over its keys, i.e. p(key) = 2^(s scale log2e - m) / l
   int32_t T, Hq, Hkv, hd;
+  bool once;                 // keys and values are marked as not wanted again
 };
 hipError_t launch_attention(const AttnLaunch& a, hipStream_t s);
 
@@ -239,6 +240,7 @@ struct StreamArgs {
   void* c;               // f32 [M][N]; SwiGLU: [M][N / 2 / 32][hi 32 | lo 32]
   int32_t M, N, K;       // N: weight rows in all (gate + up for SwiGLU)
   int32_t epilogue, half_units;
+  bool once;             // the weights are marked as not wanted again
   float out_scale, c_scale;   // as in GemmArgs
   BatchMeta meta;        // QKV only, and below
   const float2* cs;
