@@ -667,9 +667,10 @@ static int32_t run_stream(StreamArgs g, int epi, const void* a, float a_scale, c
 // cbuf is left alone; otherwise *n_parts = 0 and cbuf holds the result.
 static int32_t run_gemm(const uint16_t* a, const uint16_t* a_lo, float a_scale, const void* w0, int r0, const void* w1,
                         int r1, const void* w2, int r2, void* cbuf, void* cbuf_lo, int M, int N, int K, int epi,
-                        hipStream_t s, float* parts = nullptr, int* n_parts = nullptr, bool a_paired = false,
+                        hipStream_t s, bool once, float* parts = nullptr, int* n_parts = nullptr, bool a_paired = false,
                         bool c_paired = false) {
-  GemmArgs g;
+  GemmArgs g{};
+  g.once = once;
   g.a = a;
   g.a_lo = a_paired ? nullptr : a_lo;
   g.a_paired = a_paired;
@@ -790,7 +791,7 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
       {
         StageTimer t(c, SYNERA_STAGE_QKV, s);
         if ((st = run_gemm(c->y, c->y_lo, SY_Y_SCALE, w.wq, qd, w.wk, kd, w.wv, kd, c->qkv, nullptr, T, qd + 2 * kd, d,
-                           GEMM_STORE_F32, s, c->gparts, &qkv_parts, pair_qkv)))
+                           GEMM_STORE_F32, s, c->weights_once, c->gparts, &qkv_parts, pair_qkv)))
           return st;
       }
       {
@@ -829,7 +830,7 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
     {
       StageTimer t(c, SYNERA_STAGE_O, s);
       if ((st = run_gemm(c->o, c->o_lo, SY_O_SCALE, w.wo, d, nullptr, 0, nullptr, 0, c->x, nullptr, T, d, qd,
-                         GEMM_ADD_F32, s, c->gparts, &pend, pair_o)))
+                         GEMM_ADD_F32, s, c->weights_once, c->gparts, &pend, pair_o)))
         return st;
     }
     {
@@ -841,14 +842,14 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
     {
       StageTimer t(c, SYNERA_STAGE_GATE_UP, s);
       if ((st = run_gemm(c->y, c->y_lo, SY_Y_SCALE, w.w_gate, 0, w.w_up, 0, nullptr, 0, c->act,
-                         c->act_lo, T, 2 * m.d_ffn, d, GEMM_SWIGLU, s, nullptr, nullptr, pair_gu, pair_down)))
+                         c->act_lo, T, 2 * m.d_ffn, d, GEMM_SWIGLU, s, c->weights_once, nullptr, nullptr, pair_gu, pair_down)))
         return st;
     }
     if (lo_off & LO_DOWN_IN) HIP_TRY(launch_fill_zero(reinterpret_cast<float*>(c->act_lo), (size_t)T * m.d_ffn / 2, s));
     {
       StageTimer t(c, SYNERA_STAGE_DOWN, s);
       if ((st = run_gemm(c->act, c->act_lo, SY_ACT_SCALE, w.w_down, d, nullptr, 0, nullptr, 0, c->x, nullptr, T, d,
-                         m.d_ffn, GEMM_ADD_F32, s, c->gparts, &pend, pair_down)))
+                         m.d_ffn, GEMM_ADD_F32, s, c->weights_once, c->gparts, &pend, pair_down)))
         return st;
     }
   }
@@ -873,7 +874,7 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
                            m.vocab, d, s)))
         return st;
     } else if ((st = run_gemm(c->ysel, ysel_lo, SY_Y_SCALE, c->lm_head, m.vocab, nullptr, 0, nullptr, 0, logits, nullptr,
-                       p.R_all, m.vocab, d, GEMM_STORE_F32, s)))
+                       p.R_all, m.vocab, d, GEMM_STORE_F32, s, c->weights_once)))
       return st;
   }
   float* p_out = (d_top1_prob && !extra) ? d_top1_prob : c->lm_p;
@@ -1236,7 +1237,7 @@ extern "C" int32_t synera_debug_gemm_epilogue(const void* d_a, const void* d_a_l
   const bool glu = epilogue == GEMM_SWIGLU;
   return run_gemm(static_cast<const uint16_t*>(d_a), static_cast<const uint16_t*>(d_a_lo), 1.0f, d_w0, glu ? N / 2 : N,
                   glu ? d_w1 : nullptr, glu ? N / 2 : 0, nullptr, 0, d_c, d_c_lo, M, N, K, epilogue,
-                  static_cast<hipStream_t>(stream));
+                  static_cast<hipStream_t>(stream), true);
 }
 
 extern "C" int32_t synera_debug_gemm_paired(const void* d_a_pairs, const void* d_w0, const void* d_w1, void* d_c,
@@ -1246,7 +1247,7 @@ extern "C" int32_t synera_debug_gemm_paired(const void* d_a_pairs, const void* d
   if (N % (epilogue == GEMM_SWIGLU ? 256 : 128) != 0 || K % 64 != 0) return SYNERA_EUNSUP;
   const bool glu = epilogue == GEMM_SWIGLU;
   return run_gemm(static_cast<const uint16_t*>(d_a_pairs), nullptr, 1.0f, d_w0, glu ? N / 2 : N, glu ? d_w1 : nullptr,
-                  glu ? N / 2 : 0, nullptr, 0, d_c, nullptr, M, N, K, epilogue, static_cast<hipStream_t>(stream),
+                  glu ? N / 2 : 0, nullptr, 0, d_c, nullptr, M, N, K, epilogue, static_cast<hipStream_t>(stream), true,
                   nullptr, nullptr, true, glu);
 }
 
@@ -1258,7 +1259,7 @@ extern "C" int32_t synera_debug_gemm_slices(const void* d_a, const void* d_a_lo,
   int n_parts = 0;
   const int32_t st = run_gemm(static_cast<const uint16_t*>(d_a), static_cast<const uint16_t*>(d_a_lo), 1.0f, d_w, N,
                               nullptr, 0, nullptr, 0, d_parts, nullptr, M, N, K, GEMM_STORE_F32,
-                              static_cast<hipStream_t>(stream), d_parts, &n_parts);
+                              static_cast<hipStream_t>(stream), true, d_parts, &n_parts);
   *h_n_parts = n_parts > 0 ? n_parts : 1;
   return st;
 }
@@ -1268,7 +1269,7 @@ extern "C" int32_t synera_gemm_pair(const void* d_a, const void* d_a_lo, const v
   if (!d_a || !d_w || !d_c || M < 1 || N < 1 || K < 1) return SYNERA_EINVAL;
   if (N % 128 != 0 || K % 64 != 0) return SYNERA_EUNSUP;
   return run_gemm(static_cast<const uint16_t*>(d_a), static_cast<const uint16_t*>(d_a_lo), 1.0f, d_w, N, nullptr, 0,
-                  nullptr, 0, d_c, nullptr, M, N, K, GEMM_STORE_F32, static_cast<hipStream_t>(stream));
+                  nullptr, 0, d_c, nullptr, M, N, K, GEMM_STORE_F32, static_cast<hipStream_t>(stream), true);
 }
 
 extern "C" int32_t synera_debug_set_lo_off(synera_ctx* c, int32_t sites) {

@@ -7,6 +7,7 @@
 
 typedef uint16_t bf16_t;  // raw bf16 bits in memory
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -40,6 +41,12 @@ __device__ __forceinline__ void split_f16x2(float a, float b, uint32_t& hi, uint
   const f32x2_t r = v - __builtin_convertvector(h, f32x2_t);
   hi = __builtin_bit_cast(uint32_t, h);
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2_t));
+}
+
+// bf16 pair -> fp16 pair of 2^SY_W_SHIFT times the values (exact for normal results)
+__device__ __forceinline__ uint32_t widen_weights(uint32_t w) {
+  const uint32_t x = w + ((uint32_t)SY_W_SHIFT << 7) * 0x00010001u;
+  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(x << 16), __uint_as_float(x & 0xFFFF0000u)));
 }
 
 // One rotary pair by the angle (c, s).  Both fused operations are spelled out: left to the compiler, either product of a sum may
@@ -200,6 +207,8 @@ struct GemmArgs {
   float out_scale;       // accumulators x this = the product: 2^-SY_W_SHIFT / (the activation pair's scale)
   float c_scale;         // SWIGLU only: scale of the output pair (SY_ACT_SCALE)
   bool a_paired;         // the activations are one paired array (see a); only with tiles of one K step per stage
+  bool once;             // the weights are marked as not wanted again (tiles with stages of 64 k: they read whole lines)
+  bool rotate;           // set by the launcher: blocks start at different k
   bool c_paired;         // SWIGLU only: write the output pair as one paired array [M][N/2 / 32][hi 32 | lo 32] to c
 };
 // Element offset of column `col` inside a row of a paired array (row pitch: 2 x columns); the low part is 32 on.
@@ -214,7 +223,7 @@ int gemm_plan_bk(const GemmArgs& g);                               // K extent o
 hipError_t launch_proj_nf4_low(int mt, const GemmArgs& g, hipStream_t s);    // 256 columns, 16 .. 144 rows
 hipError_t launch_proj_nf4_high(int mt, const GemmArgs& g, hipStream_t s);   // 256 columns, 160 .. 272 rows
 hipError_t launch_proj_nf2(int mt, const GemmArgs& g, hipStream_t s);        // 128 columns, 16 .. 192 rows
-hipError_t launch_proj_k64(int mt, int nf, const GemmArgs& g, hipStream_t s);   // BK = 64: 128 columns x 16 .. 144 rows, 256 x 16 .. 80
+hipError_t launch_proj_k64(int mt, int nf, GemmArgs g, hipStream_t s);   // BK = 64: 128 columns x 16 .. 144 rows, 256 x 16 .. 80
 
 // ---------------------------------------------------------------- stream.hip
 // The projections of a batch of up to SY_STREAM_ROWS rows.

@@ -6,6 +6,7 @@
 // only 112 blocks and every block pulls its weight stream at the ~24 GB/s one compute unit sustains from HBM;
 // 224 blocks of 128 columns stream on twice the compute units.  K may be split into stored slices.
 #include "common.h"
+#include <algorithm>
 
 static int g_forced = -1;   // tuning hook: forced tile (see gemm_force_variant), -1 = automatic
 void gemm_force_variant(int v) { g_forced = v; }
@@ -23,15 +24,23 @@ static bool tile_fits(const GemmArgs& g, int mt, int nf, int ksub) {
   return true;
 }
 
-// Modelled time of one stage (32 ksub of K) of one block, us.  Fit of MI355X timings of the 8B gate/up projection at
-// M = 532 on 256-column tiles of 128, 144 and 272 rows: 0.17 us plus 0.086 us per 16-row block and MFMA K step; a
-// 128-column tile pays the activation-fragment reads of a 256-column one for half the MFMAs: 0.6x, not 0.5x.  A
-// short tile is bound by its weight stream instead: BN rows x 64 bytes per K step at the ~24 GB/s one compute
-// unit pulls from HBM.
-static double step_us(int mt, int nf, bool lo, int ksub) {
+// Modelled time of one stage (32 ksub of K) of one block, us; from timings on an MI355X.
+// Tiles with one K step per stage: 0.17 us plus 0.086 us per 16-row block (8B gate/up projection at M = 532 on 256-column tiles
+// of 128, 144 and 272 rows); a 128-column tile pays the activation-fragment reads of a 256-column one for half the MFMAs: 0.6x,
+// not 0.5x.  They ask for weights by half lines, and short ones wait for that: 70B gate/up projection as one tile of 96, 128, 160, 208 rows
+// 1.0, 1.12, 1.19, 1.35 us (0.65 + 0.055 per row block), LM heads of the high part alone 0.85 at any height.
+// Two K steps per stage: K split, the same MFMAs and whole lines at the ~24 GB/s one compute unit pulls from HBM; K whole
+// (gemm_k64_whole.hip), 8B gate/up at 32 .. 144 rows 0.55 .. 0.97 us, 256 columns (70B) at 32 .. 80 rows 1.12 .. 1.5; 1.13x
+// with several rounds of blocks, or several tiles of rows to read the same weights.
+static double step_us(const GemmArgs& g, int mt, int nf, int ksub, int split, bool one_tile, bool one_round) {
+  const bool lo = g.a_lo != nullptr || g.a_paired;
+  if (ksub == 2 && split == 1 && g.K >= 1024)
+    return (nf == 4 ? 0.9 + (lo ? 0.11 : 0.05) * mt : 0.43 + (lo ? 0.06 : 0.035) * mt) * (one_tile && one_round ? 1.0 : 1.13);
   const double mfma = 0.17 + ksub * 0.086 * mt * (nf == 4 ? 1.0 : 0.6) * (lo ? 1.0 : 0.55);   // hi alone: half the MFMAs
-  const double stream = ksub * 64 * nf * 64 / 24e3;
-  return mfma > stream ? mfma : stream;
+  double stream = ksub * 64 * nf * 64 / 24e3;
+  if (ksub == 1 && one_tile) stream = nf / 4.0 * (0.65 + 0.055 * mt);
+  if (ksub == 1 && !lo) stream = std::max(stream, nf / 4.0 * 0.85);
+  return std::max(mfma, stream);
 }
 static int max_split(const GemmArgs& g, int mt, int nf) {
   if (g.epilogue == GEMM_SWIGLU || !g.c_parts) return 1;
@@ -50,7 +59,7 @@ static double plan_cost(const GemmArgs& g, int mt, int nf, int ksub, int split) 
   const long rounds = (tiles * split + 255) / 256;
   const double steps = (double)(g.K / (32 * ksub)) / split;
   const double merge = split > 1 ? 2.4 * split * ((double)g.M * g.N / 2.2e6) : 0.0;
-  return rounds * steps * step_us(mt, nf, g.a_lo != nullptr || g.a_paired, ksub) + merge;
+  return rounds * steps * step_us(g, mt, nf, ksub, split, g.M <= 16 * mt, rounds == 1) + merge;
 }
 
 static void pick(const GemmArgs& g, int* mt_out, int* nf_out, int* ksub_out, int* split_out) {
@@ -75,6 +84,9 @@ static void pick(const GemmArgs& g, int* mt_out, int* nf_out, int* ksub_out, int
         if (!tile_fits(g, mt, nf, ksub)) continue;
         const int most = max_split(g, mt, nf);
         for (int split = 1; split <= most; ++split) {    // fewer slices than fit can win: less to merge
+          // whole K in stages of 64 (gemm_k64_whole.hip): built for the weight stream of one tile of rows; several read the
+          // same weights, and pairs of activations then make it a matter of the MFMAs
+          if (ksub == 2 && split == 1 && g.K >= 1024 && g.M > 16 * mt && g.a_lo) continue;
           const double c = plan_cost(g, mt, nf, ksub, split);
           if (best_mt < 0 || c < best_cost) {
             best_mt = mt;

@@ -1,29 +1,60 @@
-// Instantiations of the projection GEMM tile (gemm_tile.h) with two MFMA K steps per stage (BK = 64): the short
-// tiles whose three stages of 128-byte rows fit the LDS -- 128 columns x 16 .. 144 rows, 256 columns x 16 .. 80 rows.
+// The short tiles with stages of 64 k: 128 columns x 16 .. 144 rows, 256 columns x 16 .. 80 rows.  Three kernels:
+//   * K whole and at least 16 stages long: gemm_k64_whole.hip;
+//   * K split into slices, weights that no cache holds: gemm_k64_slices.hip;
+//   * the rest -- small models, whose launches are over before either pays -- here, the tile of gemm_tile.h (KSUB = 2).  (The tiny
+//     decoder, K = 256: three such launches of gemm_k64_whole.hip made a verify of 27 rows 141.4 -> 143.7 us.)
 #include "gemm_tile.h"
 
-hipError_t launch_proj_k64(int mt, int nf, const GemmArgs& g, hipStream_t s) {
+hipError_t launch_proj_k64_whole(int mt, int nf, const GemmArgs& g, hipStream_t s);
+hipError_t launch_proj_k64_slices(int mt, int nf, const GemmArgs& g, hipStream_t s);
+
+template <int MT, int NF>
+static hipError_t launch_k64(const GemmArgs& g, hipStream_t s) {
+  const int m_tiles = (g.M + 16 * MT - 1) / (16 * MT), n_tiles = g.N / (64 * NF);
+  const dim3 grid(8 * ((n_tiles + 7) / 8) * m_tiles, 1, g.split_k);
+  if (!g.a_lo) {
+    proj_kernel<MT, NF, GEMM_STORE_F32, false, 2><<<grid, 256, 0, s>>>(g);
+    return hipGetLastError();
+  }
+  switch (g.epilogue) {
+    case GEMM_STORE_F32: proj_kernel<MT, NF, GEMM_STORE_F32, true, 2><<<grid, 256, 0, s>>>(g); break;
+    case GEMM_ADD_F32: proj_kernel<MT, NF, GEMM_ADD_F32, true, 2><<<grid, 256, 0, s>>>(g); break;
+    case GEMM_SWIGLU: proj_kernel<MT, NF, GEMM_SWIGLU, true, 2><<<grid, 256, 0, s>>>(g); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_proj_k64(int mt, int nf, GemmArgs g, hipStream_t s) {
+  if (g.K % 64 != 0 || g.a_paired || (!g.a_lo && g.epilogue != GEMM_STORE_F32)) return hipErrorInvalidValue;
+  // Starting at different k spreads the blocks over the memory channels, but every XCD then reads all activations at any
+  // time: up to 3 MB of them stay in its 4 MB of L2.  (8B shape: gate/up at 64 rows, 1 MB, 57.2 -> 53.0 us, at 128, 2 MB, 70.7
+  // -> 66.8; down projection at 128, 7.3 MB, 36.5 -> 44.8.)  Short slices begin at different k as it is (QKV at 96 rows, slices
+  // of 820: 20.4 -> 20.8 us; 70B output projection at 96, 3 MB, slices of 2048: 45.4 -> 38.4).
+  g.rotate = g.M <= 16 * mt && (size_t)g.M * g.K * (g.a_lo ? 4 : 2) <= ((size_t)3 << 20) && g.K / g.split_k >= 2048;
+  if (g.split_k == 1 && g.K >= 1024) return launch_proj_k64_whole(mt, nf, g, s);
+  if (g.split_k > 1 && g.once && g.a_lo) return launch_proj_k64_slices(mt, nf, g, s);
   if (nf == 2) {
     switch (mt) {
-      case 1: return launch_proj<1, 2, 2>(g, s);
-      case 2: return launch_proj<2, 2, 2>(g, s);
-      case 3: return launch_proj<3, 2, 2>(g, s);
-      case 4: return launch_proj<4, 2, 2>(g, s);
-      case 5: return launch_proj<5, 2, 2>(g, s);
-      case 6: return launch_proj<6, 2, 2>(g, s);
-      case 7: return launch_proj<7, 2, 2>(g, s);
-      case 8: return launch_proj<8, 2, 2>(g, s);
-      case 9: return launch_proj<9, 2, 2>(g, s);
+      case 1: return launch_k64<1, 2>(g, s);
+      case 2: return launch_k64<2, 2>(g, s);
+      case 3: return launch_k64<3, 2>(g, s);
+      case 4: return launch_k64<4, 2>(g, s);
+      case 5: return launch_k64<5, 2>(g, s);
+      case 6: return launch_k64<6, 2>(g, s);
+      case 7: return launch_k64<7, 2>(g, s);
+      case 8: return launch_k64<8, 2>(g, s);
+      case 9: return launch_k64<9, 2>(g, s);
       default: return hipErrorInvalidValue;
     }
   }
   if (nf == 4) {
     switch (mt) {
-      case 1: return launch_proj<1, 4, 2>(g, s);
-      case 2: return launch_proj<2, 4, 2>(g, s);
-      case 3: return launch_proj<3, 4, 2>(g, s);
-      case 4: return launch_proj<4, 4, 2>(g, s);
-      case 5: return launch_proj<5, 4, 2>(g, s);
+      case 1: return launch_k64<1, 4>(g, s);
+      case 2: return launch_k64<2, 4>(g, s);
+      case 3: return launch_k64<3, 4>(g, s);
+      case 4: return launch_k64<4, 4>(g, s);
+      case 5: return launch_k64<5, 4>(g, s);
       default: return hipErrorInvalidValue;
     }
   }

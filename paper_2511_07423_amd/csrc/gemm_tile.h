@@ -17,9 +17,9 @@
 //
 // Tile: BM = 16 MT rows x BN = 64 NF columns, four wavefronts (one per SIMD), each owning all BM rows of 16 NF
 // columns.  A stage holds BK = 32 KSUB of K: one MFMA K step (lane l holds row l % 16 and the 8 k values of chunk
-// l / 16 for both operands), or two for the short tiles (KSUB = 2: tile rows of 128 bytes, so every copy moves
-// whole cache lines, half the requests for the same bytes, and the K loop has half the barriers; small batches
-// are bound by exactly these).  The weight fragment is the MFMA's first operand, so a lane ends up with 4 consecutive output
+// l / 16 for both operands), or two for the short tiles (KSUB = 2, gemm_k64.hip: tile rows of 128 bytes, so
+// every copy moves whole cache lines, half the requests for the same bytes, and the K loop has half the barriers; small
+// batches are bound by exactly these).  The weight fragment is the MFMA's first operand, so a lane ends up with 4 consecutive output
 // columns of one row and the epilogue stores 16 bytes per lane.  Per K step a wavefront reads its NF weight
 // fragments once and streams the 2 MT activation fragments (hi, lo) through them; each activation fragment feeds
 // NF independent accumulators, which is what this 4-pass MFMA needs to issue back to back.  Accumulators 0..255
@@ -62,6 +62,11 @@ __device__ __forceinline__ uint32_t lds_addr_of(const void* p) {
 __device__ __forceinline__ void glds16_at(const void* base, uint32_t lane_off, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(lane_off), "s"(base) : "memory", "m0");
 }
+// The same, the lines marked as not wanted again (nt).  Only for whole 128-byte lines: of a line asked for in halves the second
+// half came from HBM again (weights by 64-byte rows: 110 -> 121 us where it was tried).
+__device__ __forceinline__ void glds16_once(const void* base, uint32_t lane_off, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_addr), "v"(lane_off), "s"(base) : "memory", "m0");
+}
 // Element offset of 16-byte chunk `chunk` of tile row `row` (rows of CPR = 4 or 8 chunks: 64 or 128 bytes).  A
 // fragment read (lane = row l % 16, chunk 4 ks + l / 16) is served 16 lanes per cycle over the 64 banks, lanes
 // l and l + 16 together: the chunk position varies with the row's bits 1..2 (XORed into chunk bits 0..1 of a
@@ -72,7 +77,7 @@ __device__ __forceinline__ int swz16(int row, int chunk) {
   return (row * CPR + (chunk ^ (((row >> 1) & 3) << (CPR == 8 ? 1 : 0)))) * 8;
 }
 
-template <int MT, int NF, int EPI, bool LO = true, int KSUB = 1, bool PAIRED = false>
+template <int MT, int NF, int EPI, bool LO = true, int KSUB = 1, bool PAIRED = false, bool ONCE = false, bool TURN = false>
 __global__ __launch_bounds__(256) void proj_kernel(GemmArgs g) {
   // PAIRED: the activations come as one array [M][K / 32][hi 32 | lo 32] (GemmArgs::a, a_lo unused): the 64 bytes of
   // a row's high part and the 64 of its low part for one K step are one 128-byte line, so an activation copy moves
@@ -84,6 +89,8 @@ __global__ __launch_bounds__(256) void proj_kernel(GemmArgs g) {
   constexpr int BM = 16 * MT, BN = 64 * NF, BK = 32 * KSUB;
   constexpr int CPR = BK / 8, RPI = 64 / CPR;    // 16-byte chunks per tile row; tile rows per copy instruction
   static_assert(KSUB == 1 || KSUB == 2, "one or two MFMA K steps per stage");
+  // ONCE, TURN: GemmArgs::once, rotate
+  static_assert(KSUB == 2 || !(ONCE || TURN), "weights that are not kept have to be read by whole lines");
   static_assert(NF == 2 || NF == 4, "SwiGLU pairs the fragments (gate, up): NF must be even");
   static_assert(MT >= 1 && MT <= 17, "accumulators: 4 NF MT registers per lane, stages: 3 (2 BM + BN) x 64 B of LDS");
   constexpr int TERMS = LO ? 2 : 1;              // activation terms: (hi, lo), or hi alone (LO = false: the low part is
@@ -119,6 +126,12 @@ __global__ __launch_bounds__(256) void proj_kernel(GemmArgs g) {
   const int step_begin = (int)((long)blockIdx.z * total_steps / g.split_k);
   const int n_steps = (int)((long)(blockIdx.z + 1) * total_steps / g.split_k) - step_begin;
   if (n_steps <= 0) return;
+
+  const int turn = TURN ? (int)((unsigned)n_tile * 3u % (unsigned)n_steps) : 0;   // the step to begin with
+  auto turned = [&](int s) {
+    s += turn;
+    return TURN && s >= n_steps ? s - n_steps : s;
+  };
 
   const uint16_t* src[IPW];                      // wavefront-uniform part of the copy's global address
   uint32_t off[IPW];                             // this lane's byte offset from it (constant along K)
@@ -191,7 +204,12 @@ __global__ __launch_bounds__(256) void proj_kernel(GemmArgs g) {
   // and the two packed again (exact: 8 mantissa bits into 11).  A zero becomes 2^(SY_W_SHIFT - 127) in fp32 and
   // goes back to zero in the packing.
   const uint32_t exp_add = ((uint32_t)SY_W_SHIFT << 7) * 0x00010001u, hi_mask = 0xFFFF0000u;
-#define SY_COPY(J_, NXT, STEP) glds16_at(src[J_] + (size_t)(STEP) * (PAIRED && (J_) < A_IPW ? 64 : BK), off[J_], NXT + dst[J_]);
+#define SY_COPY(J_, NXT, STEP)                                                                    \
+  {                                                                                               \
+    const uint16_t* from_ = src[J_] + (size_t)(STEP) * (PAIRED && (J_) < A_IPW ? 64 : BK);        \
+    if (ONCE && (J_) >= A_IPW) glds16_once(from_, off[J_], NXT + dst[J_]);                        \
+    else glds16_at(from_, off[J_], NXT + dst[J_]);                                                \
+  }
 #define SY_ISSUE(NXT, STEP) _Pragma("unroll") for (int j = 0; j < IPW; ++j) SY_COPY(j, NXT, STEP)
 #define SY_MFMA(ACC, FW, FA, I_)                                                                  \
   {                                                                                               \
@@ -269,15 +287,15 @@ __global__ __launch_bounds__(256) void proj_kernel(GemmArgs g) {
   {                                                                                               \
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(IPW) : "memory");                         \
     asm volatile("s_barrier" ::: "memory");                                                       \
-    const int nxt_ = (S_) + 2 < n_steps ? (S_) + 2 : n_steps - 1;                                 \
+    const int nxt_ = turned((S_) + 2 < n_steps ? (S_) + 2 : n_steps - 1);                         \
     SY_MULT(CUR, NXT, nxt_, NEXTSTAGE)                                                            \
     if (SETTLE) asm volatile("s_nop 15" ::: "memory");                                            \
   }
 
   const uint32_t l0 = lds_addr_of(st0), l1 = lds_addr_of(st1), l2 = lds_addr_of(st2);
-  SY_ISSUE(l0, 0)
+  SY_ISSUE(l0, turned(0))
   {
-    const int one_ = n_steps > 1 ? 1 : 0;
+    const int one_ = turned(n_steps > 1 ? 1 : 0);
     SY_ISSUE(l1, one_)
   }
   // the first step's weights: own copies of stage 0 have landed once at most the IPW younger ones are in flight
@@ -373,34 +391,30 @@ __global__ __launch_bounds__(256) void proj_kernel(GemmArgs g) {
   }
 }
 
-template <int MT, int NF, int KSUB = 1>
+template <int MT, int NF>
 static hipError_t launch_proj(const GemmArgs& g, hipStream_t s) {
   constexpr int BM = 16 * MT;
   const int m_tiles = (g.M + BM - 1) / BM, n_tiles = g.N / (64 * NF);
   const dim3 grid(8 * ((n_tiles + 7) / 8) * m_tiles, 1, g.split_k);
-  if (g.K % (32 * KSUB) != 0) return hipErrorInvalidValue;
+  if (g.K % 32 != 0) return hipErrorInvalidValue;
   if (!g.a_lo && !g.a_paired) {                  // single-term activations: the plain store form only
     if (g.epilogue != GEMM_STORE_F32) return hipErrorInvalidValue;
-    proj_kernel<MT, NF, GEMM_STORE_F32, false, KSUB><<<grid, 256, 0, s>>>(g);
+    proj_kernel<MT, NF, GEMM_STORE_F32, false><<<grid, 256, 0, s>>>(g);
     return hipGetLastError();
   }
-  if (g.a_paired) {                              // one array [M][K / 32][hi | lo]: the forms with one K step per stage
-    if constexpr (KSUB == 1) {
-      switch (g.epilogue) {
-        case GEMM_STORE_F32: proj_kernel<MT, NF, GEMM_STORE_F32, true, 1, true><<<grid, 256, 0, s>>>(g); break;
-        case GEMM_ADD_F32: proj_kernel<MT, NF, GEMM_ADD_F32, true, 1, true><<<grid, 256, 0, s>>>(g); break;
-        case GEMM_SWIGLU: proj_kernel<MT, NF, GEMM_SWIGLU, true, 1, true><<<grid, 256, 0, s>>>(g); break;
-        default: return hipErrorInvalidValue;
-      }
-      return hipGetLastError();
-    } else {
-      return hipErrorInvalidValue;
+  if (g.a_paired) {                              // one array [M][K / 32][hi | lo]
+    switch (g.epilogue) {
+      case GEMM_STORE_F32: proj_kernel<MT, NF, GEMM_STORE_F32, true, 1, true><<<grid, 256, 0, s>>>(g); break;
+      case GEMM_ADD_F32: proj_kernel<MT, NF, GEMM_ADD_F32, true, 1, true><<<grid, 256, 0, s>>>(g); break;
+      case GEMM_SWIGLU: proj_kernel<MT, NF, GEMM_SWIGLU, true, 1, true><<<grid, 256, 0, s>>>(g); break;
+      default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
   }
   switch (g.epilogue) {
-    case GEMM_STORE_F32: proj_kernel<MT, NF, GEMM_STORE_F32, true, KSUB><<<grid, 256, 0, s>>>(g); break;
-    case GEMM_ADD_F32: proj_kernel<MT, NF, GEMM_ADD_F32, true, KSUB><<<grid, 256, 0, s>>>(g); break;
-    case GEMM_SWIGLU: proj_kernel<MT, NF, GEMM_SWIGLU, true, KSUB><<<grid, 256, 0, s>>>(g); break;
+    case GEMM_STORE_F32: proj_kernel<MT, NF, GEMM_STORE_F32, true><<<grid, 256, 0, s>>>(g); break;
+    case GEMM_ADD_F32: proj_kernel<MT, NF, GEMM_ADD_F32, true><<<grid, 256, 0, s>>>(g); break;
+    case GEMM_SWIGLU: proj_kernel<MT, NF, GEMM_SWIGLU, true><<<grid, 256, 0, s>>>(g); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -28,7 +28,6 @@
 namespace {
 constexpr int UNIT = 4096, STAGE_K = 128, WAVES = 8;
 constexpr int SPARE = 32768;                       // LDS beside the rings of a kernel that normalises: gains, row sums
-typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
@@ -58,11 +57,6 @@ __device__ __forceinline__ void copy_unit(const void* base0, const void* base1, 
   else SY_UNIT_COPIES("");
 }
 #undef SY_UNIT_COPIES
-// bf16 pair -> fp16 pair of 2^SY_W_SHIFT times the values (exact for normal results)
-__device__ __forceinline__ uint32_t widen(uint32_t w) {
-  const uint32_t x = w + ((uint32_t)SY_W_SHIFT << 7) * 0x00010001u;
-  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(x << 16), __uint_as_float(x & 0xFFFF0000u)));
-}
 template <int... P, class F>
 __device__ __forceinline__ void each(std::integer_sequence<int, P...>, F&& f) {
   (f(std::integral_constant<int, P>{}), ...);
@@ -272,7 +266,7 @@ __global__ __launch_bounds__(64 * WAVES) void stream_kernel(StreamArgs g) {
       for (int s = 0; s < 4; ++s) {
         u32x4 wide;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) wide[q] = widen(raw[s][q]);
+        for (int q = 0; q < 4; ++q) wide[q] = widen_weights(raw[s][q]);
         const f16x8 wf = __builtin_bit_cast(f16x8, wide);
         acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf, hi[s], acc[f], 0, 0, 0);
         if (NA == 2) acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf, lo[s], acc[f], 0, 0, 0);

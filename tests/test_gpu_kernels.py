@@ -470,6 +470,30 @@ def test_gemm_stored_k_slices_sum_to_the_product(tile, M, N, K):
     assert (parts.double().sum(0) - want).abs().max().item() < 6e-9 * K + 2e-7
 
 
+@pytest.mark.parametrize("tile", [-1, 301, 302, 303, 305, 309, 203, 205])
+@pytest.mark.parametrize("M,N,K", [(17, 256, 960), (33, 512, 1024), (130, 16384, 4160), (50, 16384, 4160)])
+def test_gemm_short_tiles_whole_and_sliced(tile, M, N, K):
+    """Stages of 64 k either side of the line between the kernels that take whole K (from K = 1024), and blocks that start at
+    different k: whole K, and two slices of about 2080 (128 column tiles leave room for two), with odd numbers of steps and of row
+    blocks.  Bounds as in test_gemm_every_tile_and_epilogue."""
+    synera = _synera()
+    g = torch.Generator(device=DEV).manual_seed(31 * M + N + K)
+    a, al = synera.split_pair(torch.randn((M, K), generator=g, device=DEV))
+    w = wl.draw_normal_bf16((N, K), 0.02, 29 * N + K, DEV)
+    want = (a.double() + al.double()) @ w.double().T
+    synera.debug_set_gemm_tile(tile)
+    try:
+        got = [synera.gemm_pair(a, al, w), synera.debug_gemm_slices(a, al, w).double().sum(0)]
+        high = synera.gemm_pair(a, None, w)
+        torch.cuda.synchronize()
+    finally:
+        synera.debug_set_gemm_tile(-1)
+    tol = 6e-9 * K + 2e-7
+    for c in got:
+        assert (c.double() - want).abs().max().item() < tol
+    assert (high.double() - a.double() @ w.double().T).abs().max().item() < tol
+
+
 def test_gemm_rejects_unsupported_shapes():
     synera = _synera()
     a = torch.zeros((4, 96), dtype=torch.float16, device=DEV)
