@@ -21,7 +21,7 @@
 // lengths -> page table -> keys, four latencies of a loaded memory system (129 us for the keys alone).  A small
 // kernel folds that chain into one record per item beforehand.
 // Bound by HBM (the K pages): 128 requests, 147 K keys, 302 MB: 429 us with one thread per key and scalar FMAs
-// (5 GFLOP on the vector unit), 97 us.
+// (5 GFLOP on the vector unit), 91 us.
 #include "common.h"
 
 #define SY_CONST_AS __attribute__((address_space(4)))
@@ -55,7 +55,8 @@ __device__ __forceinline__ int imp_swz(int row) {
 
 #define IMP_ROWS 32              // query rows staged at a time
 
-template <int HD>
+// ONCE: the keys are marked as not wanted again (nt).
+template <int HD, bool ONCE>
 __global__ __launch_bounds__(256, 2) void importance_kernel(ImportanceLaunch a, int item0, int n_batch, float scale_log2) {
   constexpr int KS = HD / 32;                        // MFMA K steps over the head dimension
   constexpr int CPR = HD / 8;                        // 16-byte chunks of a row's high (or low) part
@@ -83,8 +84,10 @@ __global__ __launch_bounds__(256, 2) void importance_kernel(ImportanceLaunch a, 
 #pragma unroll
     for (int pg = 0; pg < 4; ++pg)
 #pragma unroll
-      for (int j = 0; j < KL; ++j)
-        kr[pg][j] = *reinterpret_cast<const u32x4*>(a.k_layer + ((size_t)r.pages[pg] * Hkv + kh) * SY_PAGE * HD + (j * 64 + lane) * 8);
+      for (int j = 0; j < KL; ++j) {
+        const auto* at = reinterpret_cast<const u32x4*>(a.k_layer + ((size_t)r.pages[pg] * Hkv + kh) * SY_PAGE * HD + (j * 64 + lane) * 8);
+        kr[pg][j] = ONCE ? __builtin_nontemporal_load(at) : *at;
+      }
   };
   auto load_q = [&](const Unit& r, int kh, int r0, u32x4 (&qr)[QL], float2& ml) {
     {
@@ -215,6 +218,10 @@ __global__ __launch_bounds__(256) void importance_sum_kernel(ImportanceLaunch a,
 hipError_t launch_importance(const ImportanceLaunch& a, hipStream_t s) {
   if (a.n_items <= 0) return hipSuccess;
   if (!a.parts || a.parts_cap < (size_t)a.Hkv * 256 || !a.records) return hipErrorInvalidValue;
+  if (a.hd != 128 && a.hd != 64) return hipErrorInvalidValue;
+  // Keys that the last-level cache would hardly hold beside what else a verify touches are read as not wanted again: 302 MB 93.3 ->
+  // 91.2 us.  Below, a cache may hold them.
+  const bool once = (size_t)a.n_items * 256 * a.Hkv * a.hd * 2 > ((size_t)128 << 20);
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)a.hd);
   importance_items_kernel<<<(a.n_items + 15) / 16, 256, 0, s>>>(a);
   // as many items per pass as the scratch holds shares for (one pass on every workload measured)
@@ -223,9 +230,9 @@ hipError_t launch_importance(const ImportanceLaunch& a, hipStream_t s) {
   for (int item0 = 0; item0 < a.n_items; item0 += per_pass) {
     const int n_batch = a.n_items - item0 < per_pass ? a.n_items - item0 : per_pass;
     const int grid = (int)((long)n_batch * a.Hkv < a.blocks ? (long)n_batch * a.Hkv : a.blocks);
-    if (a.hd == 128) importance_kernel<128><<<grid, 256, 0, s>>>(a, item0, n_batch, scale_log2);
-    else if (a.hd == 64) importance_kernel<64><<<grid, 256, 0, s>>>(a, item0, n_batch, scale_log2);
-    else return hipErrorInvalidValue;
+    auto* kernel = a.hd == 128 ? (once ? importance_kernel<128, true> : importance_kernel<128, false>)
+                               : (once ? importance_kernel<64, true> : importance_kernel<64, false>);
+    kernel<<<grid, 256, 0, s>>>(a, item0, n_batch, scale_log2);
     importance_sum_kernel<<<n_batch, 256, 0, s>>>(a, item0, n_batch);
   }
   return hipGetLastError();
