@@ -46,6 +46,18 @@ def test_topk_matches_oracle(dtype, rows, vocab, k):
     _check_topk(x, k, f"{rows}x{vocab} k={k}")
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("pieces", [1, 511, 2047, 2049, 4096, 4097, 8193, 12289, 16383])
+def test_topk_of_rows_around_whole_rounds_of_loads(dtype, pieces):
+    """`pieces` 16-byte loads and a ragged tail: 512 threads, four loads of each on their way, 8, 16 or 32 in all."""
+    vocab = pieces * (4 if dtype == torch.float32 else 8) + 3
+    g = torch.Generator(device=DEV).manual_seed(pieces)
+    x = (torch.randn((3, (vocab + 7) // 8 * 8), generator=g, device=DEV) * 3).to(dtype)[:, :vocab]
+    x[1, -1] = 40.0                                  # the tail's last entry leads
+    x[2, : vocab - 2] = float("-inf")
+    _check_topk(x, min(vocab, 9), f"{pieces} pieces")
+
+
 def test_topk_ties_plateaus_and_degenerate_rows():
     V = 4096
     x = torch.zeros((6, V), device=DEV)

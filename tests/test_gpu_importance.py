@@ -90,3 +90,39 @@ def test_importance_scores_match_the_oracle(shape):
         ver.importance(ctx, unc, k, n_pages, kp)
     assert e.value.status == synera.EINVAL
     ver.close()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_importance_of_a_request_does_not_depend_on_the_batch(head_dim):
+    """Keys of more than 128 MB (read past the caches) against the same requests one by one: what differs is where the attention's
+    key streams are cut, so the softmax statistics by a rounding, and the summation order of
+    the projections behind the queries (pairs, about 2e-5); an appended
+    K value whose rounding to bf16 falls the other way moves one score in 1600 by about 3e-4.  Bound 1e-4 of the norm."""
+    import paper_2511_07423_amd as synera
+    kv = 1024 // head_dim
+    shape = wl.ModelShape("wide_kv", 1, 1024, kv, kv, head_dim, 256, 256)
+    head = wl.draw_head_weights(shape, 51, DEV)
+    layers = [wl.draw_layer_weights(shape, 51, 0, DEV)]
+    g = torch.Generator(device=DEV).manual_seed(52)
+    B, unc = 41, np.zeros(41, np.int32)
+    ctx, k = (1617 + 3 * np.arange(B)).astype(np.int32), (1 + np.arange(B) % 9).astype(np.int32)
+    assert int((ctx + k).sum()) * kv * head_dim * 2 > 128 << 20
+    per = int((ctx + k + 15).max()) // 16
+    bt = np.arange(B * per, dtype=np.int32).reshape(B, per)
+    kp = torch.empty((1, B * per, kv, 16, head_dim), dtype=torch.bfloat16, device=DEV).normal_(generator=g)
+    vp = torch.empty((1, B * per, kv, head_dim, 16), dtype=torch.bfloat16, device=DEV).normal_(generator=g)
+    tokens = torch.randint(0, 256, (int(k.sum()),), generator=g, device=DEV, dtype=torch.int32)
+    anchor = torch.zeros(B, dtype=torch.int32, device=DEV)
+    ver = synera.Verifier(shape, head, layers, max_batch=B, max_tokens=int(k.sum()), max_pages=per)
+    ver.verify(ctx, unc, k, tokens, anchor, bt, B * per, kp, vp)
+    out = ver.importance(ctx, unc, k, B * per, kp)
+    scores, off, starts = out["scores"].clone(), out["offsets"], np.concatenate([[0], np.cumsum(k)])
+    for i in (0, 8, 40):
+        one = slice(i, i + 1)
+        ver.verify(ctx[one], unc[one], k[one], tokens[starts[i]:starts[i + 1]].contiguous(), anchor[one].contiguous(), bt[one],
+                   B * per, kp, vp)
+        want = ver.importance(ctx[one], unc[one], k[one], B * per, kp)["scores"]
+        got = scores[off[i]:off[i + 1]]
+        assert got.shape == want.shape
+        assert (got - want).double().norm().item() <= 1e-4 * want.double().norm().item()
+    ver.close()
