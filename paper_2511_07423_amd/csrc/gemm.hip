@@ -24,26 +24,34 @@ static bool tile_fits(const GemmArgs& g, int mt, int nf, int ksub) {
   return true;
 }
 
+// Whether this launch may store K slices.  Their number is the order of its sums, and the K and V rows that a layer appends round
+// to bf16 by it, so a model's outputs move with it (8 layers of the 70B shape, 126 rows over short contexts: logits by about 6e-4 of
+// their norm, and single ids, with other slices for QKV, output and down projection).
+static bool may_slice(const GemmArgs& g) { return g.epilogue != GEMM_SWIGLU && g.c_parts; }
+
 // Modelled time of one stage (32 ksub of K) of one block, us; from timings on an MI355X.
-// Tiles with one K step per stage: 0.17 us plus 0.086 us per 16-row block (8B gate/up projection at M = 532 on 256-column tiles
-// of 128, 144 and 272 rows); a 128-column tile pays the activation-fragment reads of a 256-column one for half the MFMAs: 0.6x,
-// not 0.5x.  They ask for weights by half lines, and short ones wait for that: 70B gate/up projection as one tile of 96, 128, 160, 208 rows
-// 1.0, 1.12, 1.19, 1.35 us (0.65 + 0.055 per row block), LM heads of the high part alone 0.85 at any height.
-// Two K steps per stage: K split, the same MFMAs and whole lines at the ~24 GB/s one compute unit pulls from HBM; K whole
-// (gemm_k64_whole.hip), 8B gate/up at 32 .. 144 rows 0.55 .. 0.97 us, 256 columns (70B) at 32 .. 80 rows 1.12 .. 1.5; 1.13x
-// with several rounds of blocks, or several tiles of rows to read the same weights.
-static double step_us(const GemmArgs& g, int mt, int nf, int ksub, int split, bool one_tile, bool one_round) {
+// Launches that may be sliced: 0.17 us plus 0.086 us per 16-row block and MFMA K step (8B gate/up projection at M = 532 on 256-column
+// tiles of 128, 144 and 272 rows); a 128-column tile pays the activation-fragment reads of a 256-column one for half the
+// MFMAs: 0.6x, not 0.5x.  A short tile is bound by its weight stream instead: BN rows x 64 bytes per K step at the ~24 GB/s one
+// compute unit pulls from HBM.  This fit stays as it is: see may_slice.
+// Whole K: tiles with one K step per stage ask for weights by half lines, and short ones wait for that: 70B gate/up projection as one
+// tile of 96, 128, 160, 208 rows 1.0, 1.12, 1.19, 1.35 us (0.65 + 0.055 per row block), LM heads of the high part alone 0.85
+// at any height.  Two K steps per stage (gemm_k64_whole.hip), 8B gate/up at 32 .. 144 rows 0.55 .. 0.97 us, 256 columns (70B) at
+// 32 .. 80 rows 1.12 .. 1.5; 1.13x with several rounds of blocks, or several tiles of rows to read the same weights.
+static double step_us(const GemmArgs& g, int mt, int nf, int ksub, bool one_tile, bool one_round) {
   const bool lo = g.a_lo != nullptr || g.a_paired;
-  if (ksub == 2 && split == 1 && g.K >= 1024)
+  if (!may_slice(g) && ksub == 2 && g.K >= 1024)
     return (nf == 4 ? 0.9 + (lo ? 0.11 : 0.05) * mt : 0.43 + (lo ? 0.06 : 0.035) * mt) * (one_tile && one_round ? 1.0 : 1.13);
   const double mfma = 0.17 + ksub * 0.086 * mt * (nf == 4 ? 1.0 : 0.6) * (lo ? 1.0 : 0.55);   // hi alone: half the MFMAs
   double stream = ksub * 64 * nf * 64 / 24e3;
-  if (ksub == 1 && one_tile) stream = nf / 4.0 * (0.65 + 0.055 * mt);
-  if (ksub == 1 && !lo) stream = std::max(stream, nf / 4.0 * 0.85);
+  if (!may_slice(g) && ksub == 1) {
+    if (one_tile) stream = nf / 4.0 * (0.65 + 0.055 * mt);
+    if (!lo) stream = std::max(stream, nf / 4.0 * 0.85);
+  }
   return std::max(mfma, stream);
 }
 static int max_split(const GemmArgs& g, int mt, int nf) {
-  if (g.epilogue == GEMM_SWIGLU || !g.c_parts) return 1;
+  if (!may_slice(g)) return 1;
   const long tiles = (long)((g.M + 16 * mt - 1) / (16 * mt)) * (g.N / (64 * nf));
   long split = 256 / tiles;
   const long most = g.K / 32 / 8;               // at least 8 K steps per slice
@@ -59,7 +67,7 @@ static double plan_cost(const GemmArgs& g, int mt, int nf, int ksub, int split) 
   const long rounds = (tiles * split + 255) / 256;
   const double steps = (double)(g.K / (32 * ksub)) / split;
   const double merge = split > 1 ? 2.4 * split * ((double)g.M * g.N / 2.2e6) : 0.0;
-  return rounds * steps * step_us(g, mt, nf, ksub, split, g.M <= 16 * mt, rounds == 1) + merge;
+  return rounds * steps * step_us(g, mt, nf, ksub, g.M <= 16 * mt, rounds == 1) + merge;
 }
 
 static void pick(const GemmArgs& g, int* mt_out, int* nf_out, int* ksub_out, int* split_out) {
@@ -86,7 +94,7 @@ static void pick(const GemmArgs& g, int* mt_out, int* nf_out, int* ksub_out, int
         for (int split = 1; split <= most; ++split) {    // fewer slices than fit can win: less to merge
           // whole K in stages of 64 (gemm_k64_whole.hip): built for the weight stream of one tile of rows; several read the
           // same weights, and pairs of activations then make it a matter of the MFMAs
-          if (ksub == 2 && split == 1 && g.K >= 1024 && g.M > 16 * mt && g.a_lo) continue;
+          if (!may_slice(g) && ksub == 2 && g.K >= 1024 && g.M > 16 * mt && g.a_lo) continue;
           const double c = plan_cost(g, mt, nf, ksub, split);
           if (best_mt < 0 || c < best_cost) {
             best_mt = mt;

@@ -40,6 +40,37 @@ def test_decode_sized_batches_use_tiles_of_their_own_height_and_never_atomics():
             assert synera.debug_gemm_plan(M, n, k, e, stored_slices=False)[2] == 1
 
 
+# The K slices of the projections that may be sliced, from the first row count each number holds for (17 to 1100 rows); with the
+# stage's k where it moves the cuts.  They are the order of the sums, and with it the bits of every K and V row a layer appends.
+SLICES = {
+    (QKV, D, STORE): [(17, 5, 64), (145, 5, 32), (417, 3, 32), (433, 5, 32), (513, 3, 32), (529, 5, 32), (545, 2, 0)],
+    (D, D, ADD): [(17, 8, 0), (185, 4, 0), (289, 8, 0), (307, 4, 0), (321, 5, 32), (433, 4, 0), (493, 2, 0), (513, 4, 0), (555, 2, 0),
+                  (577, 4, 0), (705, 3, 32), (721, 4, 0), (769, 3, 32), (801, 4, 0), (833, 3, 32), (881, 4, 0), (917, 2, 0),
+                  (986, 1, 0), (1025, 3, 32), (1041, 2, 0)],
+    (D, F, ADD): [(17, 8, 0), (545, 4, 0), (705, 5, 32), (721, 4, 0), (1089, 3, 32)],
+    (10240, 8192, STORE): [(17, 3, 64), (81, 6, 32), (241, 3, 32), (257, 6, 32), (273, 3, 32), (417, 2, 0), (433, 3, 32), (513, 2, 0),
+                           (529, 3, 32), (545, 2, 0), (817, 1, 0)],
+    (8192, 8192, ADD): [(17, 4, 0), (81, 8, 0), (93, 4, 0), (97, 8, 0), (108, 4, 0), (113, 8, 0), (124, 4, 0), (129, 8, 0), (139, 4, 0),
+                        (145, 8, 0), (230, 4, 0), (545, 2, 0), (1089, 1, 0)],
+    (8192, 28672, ADD): [(17, 4, 0), (81, 8, 0), (273, 4, 0), (545, 2, 0), (1089, 1, 0)],
+    (768, 256, STORE): [(17, 1, 0)],
+    (256, 256, ADD): [(17, 1, 0)],
+    (256, 1024, ADD): [(17, 4, 0)],
+}
+
+
+@pytest.mark.parametrize("N,K,epi", SLICES, ids=[f"{n}x{k}" for n, k, _ in SLICES])
+def test_slices_of_the_models_are_pinned(N, K, epi):
+    """Another number of slices gives other bits everywhere: the 8B, 70B and tiny decoder's, row count by row count."""
+    seen = []
+    for M in range(17, 1101):
+        split = synera.debug_gemm_plan(M, N, K, epi)[2]
+        stage = synera.debug_gemm_plan_bk(M, N, K, epi) if (K // 64) % split else 0
+        if not seen or seen[-1][1:] != (split, stage):
+            seen.append((M, split, stage))
+    assert seen == SLICES[N, K, epi]
+
+
 @pytest.mark.parametrize("stored", [True, False])
 @pytest.mark.parametrize("M", [1, 17, 96, 97, 130, 200, 333, 532, 777, 1030, 2048])
 @pytest.mark.parametrize("N,K,epi", [(QKV, D, STORE), (D, D, ADD), (2 * F, D, SWIGLU), (D, F, ADD), (VOCAB, D, STORE),
