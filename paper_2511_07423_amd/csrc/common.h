@@ -208,7 +208,7 @@ struct GemmArgs {
   float c_scale;         // SWIGLU only: scale of the output pair (SY_ACT_SCALE)
   bool a_paired;         // the activations are one paired array (see a); only with tiles of one K step per stage
   bool once;             // the weights are marked as not wanted again (tiles with stages of 64 k: they read whole lines)
-  bool rotate;           // set by the launcher: blocks start at different k
+  bool rotate;           // set by the launcher: blocks start at different k (high part alone, K whole)
   bool c_paired;         // SWIGLU only: write the output pair as one paired array [M][N/2 / 32][hi 32 | lo 32] to c
 };
 // Element offset of column `col` inside a row of a paired array (row pitch: 2 x columns); the low part is 32 on.
@@ -223,7 +223,7 @@ int gemm_plan_bk(const GemmArgs& g);                               // K extent o
 hipError_t launch_proj_nf4_low(int mt, const GemmArgs& g, hipStream_t s);    // 256 columns, 16 .. 144 rows
 hipError_t launch_proj_nf4_high(int mt, const GemmArgs& g, hipStream_t s);   // 256 columns, 160 .. 272 rows
 hipError_t launch_proj_nf2(int mt, const GemmArgs& g, hipStream_t s);        // 128 columns, 16 .. 192 rows
-hipError_t launch_proj_k64(int mt, int nf, GemmArgs g, hipStream_t s);   // BK = 64: 128 columns x 16 .. 144 rows, 256 x 16 .. 80
+hipError_t launch_proj_k64(int mt, int nf, const GemmArgs& g, hipStream_t s);   // BK = 64: 128 columns x 16 .. 144 rows, 256 x 16 .. 80
 
 // ---------------------------------------------------------------- stream.hip
 // The projections of a batch of up to SY_STREAM_ROWS rows.

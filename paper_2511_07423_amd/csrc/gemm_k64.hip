@@ -5,7 +5,7 @@
 //     decoder, K = 256: three such launches of gemm_k64_whole.hip made a verify of 27 rows 141.4 -> 143.7 us.)
 #include "gemm_tile.h"
 
-hipError_t launch_proj_k64_whole(int mt, int nf, const GemmArgs& g, hipStream_t s);
+hipError_t launch_proj_k64_whole(int mt, int nf, GemmArgs g, hipStream_t s);
 hipError_t launch_proj_k64_slices(int mt, int nf, const GemmArgs& g, hipStream_t s);
 
 template <int MT, int NF>
@@ -25,13 +25,8 @@ static hipError_t launch_k64(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_proj_k64(int mt, int nf, GemmArgs g, hipStream_t s) {
+hipError_t launch_proj_k64(int mt, int nf, const GemmArgs& g, hipStream_t s) {
   if (g.K % 64 != 0 || g.a_paired || (!g.a_lo && g.epilogue != GEMM_STORE_F32)) return hipErrorInvalidValue;
-  // Starting at different k spreads the blocks over the memory channels, but every XCD then reads all activations at any
-  // time: up to 3 MB of them stay in its 4 MB of L2.  (8B shape: gate/up at 64 rows, 1 MB, 57.2 -> 53.0 us, at 128, 2 MB, 70.7
-  // -> 66.8; down projection at 128, 7.3 MB, 36.5 -> 44.8.)  Short slices begin at different k as it is (QKV at 96 rows, slices
-  // of 820: 20.4 -> 20.8 us; 70B output projection at 96, 3 MB, slices of 2048: 45.4 -> 38.4).
-  g.rotate = g.M <= 16 * mt && (size_t)g.M * g.K * (g.a_lo ? 4 : 2) <= ((size_t)3 << 20) && g.K / g.split_k >= 2048;
   if (g.split_k == 1 && g.K >= 1024) return launch_proj_k64_whole(mt, nf, g, s);
   if (g.split_k > 1 && g.once && g.a_lo) return launch_proj_k64_slices(mt, nf, g, s);
   if (nf == 2) {

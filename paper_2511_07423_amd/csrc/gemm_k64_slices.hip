@@ -9,8 +9,7 @@ static hipError_t launch_slices(const GemmArgs& g, hipStream_t s) {
   const int m_tiles = (g.M + 16 * MT - 1) / (16 * MT), n_tiles = g.N / (64 * NF);
   const dim3 grid(8 * ((n_tiles + 7) / 8) * m_tiles, 1, g.split_k);
   // (a slice is stored plainly, whatever the epilogue of the whole)
-  if (g.rotate) proj_kernel<MT, NF, GEMM_STORE_F32, true, 2, false, true, true><<<grid, 256, 0, s>>>(g);
-  else proj_kernel<MT, NF, GEMM_STORE_F32, true, 2, false, true, false><<<grid, 256, 0, s>>>(g);
+  proj_kernel<MT, NF, GEMM_STORE_F32, true, 2, false, true><<<grid, 256, 0, s>>>(g);
   return hipGetLastError();
 }
 

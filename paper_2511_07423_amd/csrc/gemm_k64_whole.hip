@@ -11,7 +11,7 @@
 //     of the bytes out of LDS that four wavefronts with all rows and a quarter of the columns each read;
 //   * as many stages as fit the LDS (three at 128 rows, six at 32);
 //   * tile rows of 128 bytes: whole cache lines, which are asked for once and need not be kept (GemmArgs::once);
-//   * blocks start at different k (GemmArgs::rotate): at the same k they all ask the same memory channels.
+//   * LM heads: blocks start at different k (GemmArgs::rotate).
 // 8B gate/up at 32 / 64 / 96 / 128 rows: 42.3 / 49.8 / 56.3 / 65.8 us (four wavefronts that copied and multiplied, weights kept, the
 // same k: 53.4 / 59.6 / 64.1 / 71.4; not kept and at different k: 45.5 / 53.0 / 56.8 / 66.8); LM head at 32 / 64 / 128 rows
 // 44.5 / 46.2 / 56.9 (52.8 / 56.5 / 64).  Without the MFMAs 57.6 us at 128 rows.
@@ -89,12 +89,12 @@ __global__ __launch_bounds__(768) void whole_k_kernel(GemmArgs g) {
         off[j] = (uint32_t)(lane / CPR) * (uint32_t)(2 * K) + chunk * 16;
       }
     }
-    const int turn = g.rotate ? (int)((unsigned)n_tile * 3u % (unsigned)n_steps) : 0;
+    const int turn = !LO && g.rotate ? (int)((unsigned)n_tile * 3u % (unsigned)n_steps) : 0;
     const uint32_t base = lds_addr_of(lds);
     // copy j of the stage of step s (past the end, of the last one again: never read, but the wait counts stay constants)
     auto issue = [&](int j, int s, int slot) {
       int at = (s < n_steps ? s : n_steps - 1) + turn;
-      if (at >= n_steps) at -= n_steps;
+      if (!LO && at >= n_steps) at -= n_steps;
       const uint16_t* from = src[j] + (size_t)at * BK;
       const uint32_t to = base + slot * STAGE + dst[j];
       if (j >= A_IPW && g.once) glds16_once(from, off[j], to);
@@ -268,7 +268,13 @@ static hipError_t launch_whole(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_proj_k64_whole(int mt, int nf, const GemmArgs& g, hipStream_t s) {
+hipError_t launch_proj_k64_whole(int mt, int nf, GemmArgs g, hipStream_t s) {
+  // At the same k all blocks ask the same memory channels; starting at different ones spreads them, but every XCD then reads all
+  // activations at any time: up to 3 MB of them stay in its 4 MB of L2.  The rows after it are then sums from another k on, which only
+  // the high part alone (LM heads) may be: their logits move by 4e-6 of the norm, while the K and V rows behind a gate/up projection
+  // that started elsewhere round to bf16 the other way (1e-4 of the norm in the 8B shape, 4e-4 in the 70B).  LM head at 32 / 64 / 128
+  // rows, 8B 59.8 / 62.9 / 63.8 -> 43.3 / 44.7 / 53.0 us, 70B 114 / 116 / 127 -> 85 / 88 / 102.
+  g.rotate = !g.a_lo && g.M <= 16 * mt && (size_t)g.M * g.K * 2 <= ((size_t)3 << 20) && g.K >= 2048;
   if (nf == 2) {
     switch (mt) {
       case 1: return launch_whole<1, 2>(g, s);

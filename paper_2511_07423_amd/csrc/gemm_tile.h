@@ -77,7 +77,7 @@ __device__ __forceinline__ int swz16(int row, int chunk) {
   return (row * CPR + (chunk ^ (((row >> 1) & 3) << (CPR == 8 ? 1 : 0)))) * 8;
 }
 
-template <int MT, int NF, int EPI, bool LO = true, int KSUB = 1, bool PAIRED = false, bool ONCE = false, bool TURN = false>
+template <int MT, int NF, int EPI, bool LO = true, int KSUB = 1, bool PAIRED = false, bool ONCE = false>
 __global__ __launch_bounds__(256) void proj_kernel(GemmArgs g) {
   // PAIRED: the activations come as one array [M][K / 32][hi 32 | lo 32] (GemmArgs::a, a_lo unused): the 64 bytes of
   // a row's high part and the 64 of its low part for one K step are one 128-byte line, so an activation copy moves
@@ -89,8 +89,8 @@ __global__ __launch_bounds__(256) void proj_kernel(GemmArgs g) {
   constexpr int BM = 16 * MT, BN = 64 * NF, BK = 32 * KSUB;
   constexpr int CPR = BK / 8, RPI = 64 / CPR;    // 16-byte chunks per tile row; tile rows per copy instruction
   static_assert(KSUB == 1 || KSUB == 2, "one or two MFMA K steps per stage");
-  // ONCE, TURN: GemmArgs::once, rotate
-  static_assert(KSUB == 2 || !(ONCE || TURN), "weights that are not kept have to be read by whole lines");
+  // ONCE: GemmArgs::once
+  static_assert(KSUB == 2 || !ONCE, "weights that are not kept have to be read by whole lines");
   static_assert(NF == 2 || NF == 4, "SwiGLU pairs the fragments (gate, up): NF must be even");
   static_assert(MT >= 1 && MT <= 17, "accumulators: 4 NF MT registers per lane, stages: 3 (2 BM + BN) x 64 B of LDS");
   constexpr int TERMS = LO ? 2 : 1;              // activation terms: (hi, lo), or hi alone (LO = false: the low part is
@@ -126,12 +126,6 @@ __global__ __launch_bounds__(256) void proj_kernel(GemmArgs g) {
   const int step_begin = (int)((long)blockIdx.z * total_steps / g.split_k);
   const int n_steps = (int)((long)(blockIdx.z + 1) * total_steps / g.split_k) - step_begin;
   if (n_steps <= 0) return;
-
-  const int turn = TURN ? (int)((unsigned)n_tile * 3u % (unsigned)n_steps) : 0;   // the step to begin with
-  auto turned = [&](int s) {
-    s += turn;
-    return TURN && s >= n_steps ? s - n_steps : s;
-  };
 
   const uint16_t* src[IPW];                      // wavefront-uniform part of the copy's global address
   uint32_t off[IPW];                             // this lane's byte offset from it (constant along K)
@@ -287,15 +281,15 @@ __global__ __launch_bounds__(256) void proj_kernel(GemmArgs g) {
   {                                                                                               \
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(IPW) : "memory");                         \
     asm volatile("s_barrier" ::: "memory");                                                       \
-    const int nxt_ = turned((S_) + 2 < n_steps ? (S_) + 2 : n_steps - 1);                         \
+    const int nxt_ = (S_) + 2 < n_steps ? (S_) + 2 : n_steps - 1;                                 \
     SY_MULT(CUR, NXT, nxt_, NEXTSTAGE)                                                            \
     if (SETTLE) asm volatile("s_nop 15" ::: "memory");                                            \
   }
 
   const uint32_t l0 = lds_addr_of(st0), l1 = lds_addr_of(st1), l2 = lds_addr_of(st2);
-  SY_ISSUE(l0, turned(0))
+  SY_ISSUE(l0, 0)
   {
-    const int one_ = turned(n_steps > 1 ? 1 : 0);
+    const int one_ = n_steps > 1 ? 1 : 0;
     SY_ISSUE(l1, one_)
   }
   // the first step's weights: own copies of stage 0 have landed once at most the IPW younger ones are in flight

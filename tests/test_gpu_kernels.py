@@ -494,6 +494,25 @@ def test_gemm_short_tiles_whole_and_sliced(tile, M, N, K):
     assert (high.double() - a.double() @ w.double().T).abs().max().item() < tol
 
 
+@pytest.mark.parametrize("tile", [302, 303, 308, 202, 203, 205])
+def test_gemm_slices_have_the_bits_of_the_tile_with_one_step_per_stage(tile):
+    """Eight slices of 2048: each sums its k in order, whatever the stage, the column tile or the way the weights are read."""
+    synera = _synera()
+    M, N, K = 16 * (tile % 100) - 3, 4096, 16384
+    g = torch.Generator(device=DEV).manual_seed(tile)
+    a, al = synera.split_pair(torch.randn((M, K), generator=g, device=DEV))
+    w = wl.draw_normal_bf16((N, K), 0.02, 41, DEV)
+    got = []
+    try:
+        for t in (tile, tile - 200):
+            synera.debug_set_gemm_tile(t)
+            got.append(synera.debug_gemm_slices(a, al, w).clone())
+            torch.cuda.synchronize()
+    finally:
+        synera.debug_set_gemm_tile(-1)
+    assert got[0].shape[0] == 8 and torch.equal(got[0], got[1])
+
+
 def test_gemm_rejects_unsupported_shapes():
     synera = _synera()
     a = torch.zeros((4, 96), dtype=torch.float16, device=DEV)
