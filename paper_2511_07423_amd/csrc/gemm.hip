@@ -36,12 +36,15 @@ static bool may_slice(const GemmArgs& g) { return g.epilogue != GEMM_SWIGLU && g
 // compute unit pulls from HBM.  This fit stays as it is: see may_slice.
 // Whole K: tiles with one K step per stage ask for weights by half lines, and short ones wait for that: 70B gate/up projection as one
 // tile of 96, 128, 160, 208 rows 1.0, 1.12, 1.19, 1.35 us (0.65 + 0.055 per row block), LM heads of the high part alone 0.85
-// at any height.  Two K steps per stage (gemm_k64_whole.hip), 8B gate/up at 32 .. 144 rows 0.55 .. 0.97 us, 256 columns (70B) at
-// 32 .. 80 rows 1.12 .. 1.5; 1.13x with several rounds of blocks, or several tiles of rows to read the same weights.
+// at any height.  Two K steps per stage: 8B gate/up at 32 .. 144 rows 0.69 .. 1.02 us, 256 columns (70B) at 32 .. 80 rows 1.37 .. 1.45,
+// the 70B's 96 .. 144 rows on 128 columns (two rounds of blocks) 0.87 .. 1.06; LM heads (gemm_k64_whole.hip) 1.13x with several
+// rounds of blocks, or several tiles of rows to read the same weights.
 static double step_us(const GemmArgs& g, int mt, int nf, int ksub, bool one_tile, bool one_round) {
   const bool lo = g.a_lo != nullptr || g.a_paired;
-  if (!may_slice(g) && ksub == 2 && g.K >= 1024)
-    return (nf == 4 ? 0.9 + (lo ? 0.11 : 0.05) * mt : 0.43 + (lo ? 0.06 : 0.035) * mt) * (one_tile && one_round ? 1.0 : 1.13);
+  if (!may_slice(g) && ksub == 2 && g.K >= 1024) {
+    if (lo) return nf == 4 ? 1.35 + 0.02 * mt : 0.6 + 0.048 * mt;
+    return (nf == 4 ? 0.9 + 0.05 * mt : 0.43 + 0.035 * mt) * (one_tile && one_round ? 1.0 : 1.13);
+  }
   const double mfma = 0.17 + ksub * 0.086 * mt * (nf == 4 ? 1.0 : 0.6) * (lo ? 1.0 : 0.55);   // hi alone: half the MFMAs
   double stream = ksub * 64 * nf * 64 / 24e3;
   if (!may_slice(g) && ksub == 1) {
@@ -92,8 +95,8 @@ static void pick(const GemmArgs& g, int* mt_out, int* nf_out, int* ksub_out, int
         if (!tile_fits(g, mt, nf, ksub)) continue;
         const int most = max_split(g, mt, nf);
         for (int split = 1; split <= most; ++split) {    // fewer slices than fit can win: less to merge
-          // whole K in stages of 64 (gemm_k64_whole.hip): built for the weight stream of one tile of rows; several read the
-          // same weights, and pairs of activations then make it a matter of the MFMAs
+          // pairs, whole K in stages of 64: for the weight stream of one tile of rows; several read the same weights, which makes
+          // it a matter of the MFMAs
           if (!may_slice(g) && ksub == 2 && g.K >= 1024 && g.M > 16 * mt && g.a_lo) continue;
           const double c = plan_cost(g, mt, nf, ksub, split);
           if (best_mt < 0 || c < best_cost) {

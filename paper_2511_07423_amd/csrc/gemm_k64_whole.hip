@@ -1,33 +1,30 @@
-// The projection GEMM of small batches where K is not split (gate/up, LM head) and long enough: tiles of 16 MT rows by 64 NF columns in
-// stages of 64 k, 128 columns x 16 .. 144 rows and 256 columns x 16 .. 80 rows (operand formats, columns and epilogues:
-// gemm_tile.h; which launch takes it: gemm_k64.hip).
+// LM heads of small batches: one product of the activations' high part, K whole and at least 16 stages of 64 k long, in tiles of 16 MT
+// rows by 64 NF columns (operand formats and columns: gemm_tile.h; which launch takes it: gemm_k64.hip).
 //
-// Bound: the copies -- the weight stream from HBM and, behind it, the activations out of L2.  Of the 8B gate/up matrix (235 MB, 224
-// blocks of 128 columns) the weights alone take 37 us, with 32 / 64 / 128 rows of activations 37 / 43 / 52, whatever the depth of
-// the rings or the way into registers or LDS; the launch adds about 5.  So everything else has to stay out of the copies' way:
+// Bound: the copies -- the weight stream from HBM and, behind it, the activations out of L2.  So everything else has to stay out of
+// their way:
 //   * four wavefronts only copy: a stage's place is asked for again the moment it has been read, not behind MFMAs;
 //   * eight multiply, two per SIMD, in turns: while the even halves of the stages' K are read and widened the odd ones'
-//     MFMAs run, and the other way round.  A wavefront owns half of a stage's K x half of the rows x half of the columns: two thirds
-//     of the bytes out of LDS that four wavefronts with all rows and a quarter of the columns each read;
-//   * as many stages as fit the LDS (three at 128 rows, six at 32);
+//     MFMAs run, and the other way round.  A wavefront owns half of a stage's K x half of the rows x half of the columns: at
+//     128 rows 0.8 of the bytes out of LDS that four wavefronts with all rows and a quarter of the columns each read;
+//   * as many stages as fit the LDS (up to six);
 //   * tile rows of 128 bytes: whole cache lines, which are asked for once and need not be kept (GemmArgs::once);
-//   * LM heads: blocks start at different k (GemmArgs::rotate).
-// 8B gate/up at 32 / 64 / 96 / 128 rows: 42.3 / 49.8 / 56.3 / 65.8 us (four wavefronts that copied and multiplied, weights kept, the
-// same k: 53.4 / 59.6 / 64.1 / 71.4; not kept and at different k: 45.5 / 53.0 / 56.8 / 66.8); LM head at 32 / 64 / 128 rows
-// 44.5 / 46.2 / 56.9 (52.8 / 56.5 / 64).  Without the MFMAs 57.6 us at 128 rows.
+//   * blocks start at different k (GemmArgs::rotate).
+// LM head at 32 / 64 / 128 / 256 rows, 8B 61.6 / 64.2 / 68.8 / 119 -> 43.3 / 46.1 / 55 / 100 us, 70B 112 / 116 / 128 / 228 -> 85 / 88 / 105
+// / 187 (before: the tile of gemm_tile.h).
 //
-// The two K halves are added through LDS at the end, the even half first.
-#include "gemm_tile.h"
-#include <type_traits>
+// The two K halves are added through LDS at the end, the even half first, and a row's sum may start at another k: an order of its own.
+// The logits move by 5e-7 of their norm; nothing that is rounded follows.  (Gate/up in this order moved the K and V rows behind it by
+// 1e-4 of the norm in the 8B shape, 4e-4 in the 70B: bf16 roundings that fall the other way.)
+#include "gemm_k64.h"
 
-template <int MT, int NF, int EPI, bool LO>
+template <int MT, int NF>
 __global__ __launch_bounds__(768) void whole_k_kernel(GemmArgs g) {
   constexpr int BM = 16 * MT, BN = 64 * NF, BK = 64, CPR = 8;
-  constexpr int TERMS = LO ? 2 : 1;
-  constexpr int R = TERMS * BM + BN, STAGE = R * BK * 2;         // rows [A_hi | A_lo | W] of 128 bytes
+  constexpr int R = BM + BN, STAGE = R * BK * 2;                 // rows [A | W] of 128 bytes
   constexpr int FIT = 163840 / STAGE, DEPTH = FIT < 6 ? FIT : 6;
   static_assert(DEPTH >= 3, "three stages have to fit the 160 KB of LDS");
-  constexpr int A_INS = TERMS * BM / 8;                          // copies (8 rows, 1 KB) of a stage, and per wavefront
+  constexpr int A_INS = BM / 8;                                  // copies (8 rows, 1 KB) of a stage, and per wavefront
   constexpr int A_IPW = (A_INS + 3) / 4, W_IPW = BN / 32, IPW = A_IPW + W_IPW;
   constexpr int MB = (MT + 1) / 2, NFW = 2 * NF;                 // 16-row blocks and 16-column fragments of a wavefront
   __shared__ __attribute__((aligned(16))) unsigned char lds[DEPTH * STAGE];
@@ -61,40 +58,31 @@ __global__ __launch_bounds__(768) void whole_k_kernel(GemmArgs g) {
       const int chunk = (lane % CPR) ^ (((r >> 1) & 3) << 1);      // swz16<8>, on the global side
       dst[j] = grp * 1024;
       if (j < A_IPW) {
-        const int first = grp * 8;                                 // all 8 rows lie in one array: BM is a multiple of 8
-        int am = m0 + (r < BM ? r : r - BM);
-        am = am < M ? am : M - 1;                                  // rows past M are copied (clamped) and never stored
-        src[j] = (first < BM ? g.a : g.a_lo) + (size_t)m0 * K;
+        const int am = m0 + r < M ? m0 + r : M - 1;                // rows past M are copied (clamped) and never stored
+        src[j] = g.a + (size_t)m0 * K;
         off[j] = (uint32_t)(am - m0) * (uint32_t)(2 * K) + chunk * 16;
       } else {
-        const int col = grp * 8 - TERMS * BM;
-        int wrow;
-        const bf16_t* wbase;
-        if (EPI == GEMM_SWIGLU) {                                  // 16-column groups alternate gate, up
-          wrow = (n0 >> 1) + ((col >> 5) << 4) + (col & 15);
-          wbase = ((col >> 4) & 1) ? g.w[1] : g.w[0];
-        } else {
-          wrow = n0 + col;
-          wbase = g.w[0];
-          if (wrow >= g.w_rows[0]) {
-            wrow -= g.w_rows[0];
-            wbase = g.w[1];
-            if (wrow >= g.w_rows[1]) {
-              wrow -= g.w_rows[1];
-              wbase = g.w[2];
-            }
+        const int col = grp * 8 - BM;
+        int wrow = n0 + col;
+        const bf16_t* wbase = g.w[0];
+        if (wrow >= g.w_rows[0]) {
+          wrow -= g.w_rows[0];
+          wbase = g.w[1];
+          if (wrow >= g.w_rows[1]) {
+            wrow -= g.w_rows[1];
+            wbase = g.w[2];
           }
         }
         src[j] = wbase + (size_t)wrow * K;
         off[j] = (uint32_t)(lane / CPR) * (uint32_t)(2 * K) + chunk * 16;
       }
     }
-    const int turn = !LO && g.rotate ? (int)((unsigned)n_tile * 3u % (unsigned)n_steps) : 0;
+    const int turn = g.rotate ? (int)((unsigned)n_tile * 3u % (unsigned)n_steps) : 0;
     const uint32_t base = lds_addr_of(lds);
     // copy j of the stage of step s (past the end, of the last one again: never read, but the wait counts stay constants)
     auto issue = [&](int j, int s, int slot) {
       int at = (s < n_steps ? s : n_steps - 1) + turn;
-      if (!LO && at >= n_steps) at -= n_steps;
+      if (at >= n_steps) at -= n_steps;
       const uint16_t* from = src[j] + (size_t)at * BK;
       const uint32_t to = base + slot * STAGE + dst[j];
       if (j >= A_IPW && g.once) glds16_once(from, off[j], to);
@@ -131,21 +119,18 @@ __global__ __launch_bounds__(768) void whole_k_kernel(GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < NFW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int l16 = lane & 15, kc = lane >> 4;
-  // byte offsets inside a stage; + i * 16 rows (+ BM rows: low part), + j * 16 rows.  With MT odd the last block of the second
-  // half lies behind the high (low) part's rows, still inside the stage, and is never stored.
+  // byte offsets inside a stage; + i * 16 rows, + j * 16 rows.  With MT odd the last block of the second half lies behind the
+  // activations' rows, still inside the stage, and is never stored.
   const int frag = swz16<CPR>(l16, 4 * kh + kc) * 2;
-  const int a_off = rh * MB * 16 * BK * 2 + frag, w_off = (TERMS * BM + ch * 16 * NFW) * BK * 2 + frag;
+  const int a_off = rh * MB * 16 * BK * 2 + frag, w_off = (BM + ch * 16 * NFW) * BK * 2 + frag;
 
-  u32x4 w[NFW], hi[MB], lo[MB];
+  u32x4 w[NFW], act[MB];
   auto read = [&](int slot) {                                    // this wavefront's fragments of a stage, widened
     const unsigned char* stage = lds + slot * STAGE;
 #pragma unroll
     for (int j = 0; j < NFW; ++j) w[j] = *reinterpret_cast<const u32x4*>(stage + w_off + j * 16 * BK * 2);
 #pragma unroll
-    for (int i = 0; i < MB; ++i) {
-      hi[i] = *reinterpret_cast<const u32x4*>(stage + a_off + i * 16 * BK * 2);
-      if (LO) lo[i] = *reinterpret_cast<const u32x4*>(stage + a_off + (BM + i * 16) * BK * 2);
-    }
+    for (int i = 0; i < MB; ++i) act[i] = *reinterpret_cast<const u32x4*>(stage + a_off + i * 16 * BK * 2);
 #pragma unroll
     for (int j = 0; j < NFW; ++j)
 #pragma unroll
@@ -158,11 +143,9 @@ __global__ __launch_bounds__(768) void whole_k_kernel(GemmArgs g) {
 #pragma unroll
     for (int i = 0; i < MB; ++i)
 #pragma unroll
-      for (int t = 0; t < TERMS; ++t)
-#pragma unroll
-        for (int j = 0; j < NFW; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[j]), __builtin_bit_cast(f16x8, t ? lo[i] : hi[i]),
-                                                             acc[i][j], 0, 0, 0);
+      for (int j = 0; j < NFW; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[j]), __builtin_bit_cast(f16x8, act[i]),
+                                                           acc[i][j], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -212,92 +195,25 @@ __global__ __launch_bounds__(768) void whole_k_kernel(GemmArgs g) {
     for (int i = 0; i < MB; ++i) {
       const int row = (rh * MB + i) * 16 + l16, m = m0 + row;
       if (row >= BM || m >= M) continue;
-      f32x4 v[HALF];
+      float* c = reinterpret_cast<float*>(g.c) + (size_t)m * g.N + n0 + (ch * NFW + KEEP) * 16 + nq;
 #pragma unroll
-      for (int j = 0; j < HALF; ++j) v[j] = (acc[i][KEEP + j] + other[(i * HALF + j) * 64 + lane]) * os;
-      if (EPI == GEMM_SWIGLU) {
-#pragma unroll
-        for (int j = 0; j < HALF; j += 2) {
-          float o[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) o[r] = v[j][r] / (1.0f + __expf(-v[j][r])) * v[j + 1][r] * g.c_scale;
-          uint32_t h0, l0, h1, l1;
-          split_f16x2(o[0], o[1], h0, l0);
-          split_f16x2(o[2], o[3], h1, l1);
-          const int col = (n0 >> 1) + ((ch * NFW + KEEP + j) >> 1) * 16 + nq;
-          uint16_t *at_hi, *at_lo;
-          if (g.c_paired) {
-            at_hi = reinterpret_cast<uint16_t*>(g.c) + (size_t)m * g.N + pair_col(col);
-            at_lo = at_hi + 32;
-          } else {
-            at_hi = reinterpret_cast<uint16_t*>(g.c) + (size_t)m * (g.N >> 1) + col;
-            at_lo = reinterpret_cast<uint16_t*>(g.c_lo) + (size_t)m * (g.N >> 1) + col;
-          }
-          *reinterpret_cast<uint2*>(at_hi) = make_uint2(h0, h1);
-          *reinterpret_cast<uint2*>(at_lo) = make_uint2(l0, l1);
-        }
-      } else {
-        float* c = reinterpret_cast<float*>(g.c) + (size_t)m * g.N + n0 + (ch * NFW + KEEP) * 16 + nq;
-#pragma unroll
-        for (int j = 0; j < HALF; ++j) {
-          f32x4* to = reinterpret_cast<f32x4*>(c + j * 16);
-          if (EPI == GEMM_ADD_F32) v[j] += *to;
-          *to = v[j];
-        }
-      }
+      for (int j = 0; j < HALF; ++j)
+        *reinterpret_cast<f32x4*>(c + j * 16) = (acc[i][KEEP + j] + other[(i * HALF + j) * 64 + lane]) * os;
     }
   };
   if (kh == 0) finish(std::integral_constant<int, 0>{});
   else finish(std::integral_constant<int, 1>{});
 }
 
-template <int MT, int NF>
-static hipError_t launch_whole(const GemmArgs& g, hipStream_t s) {
-  const int m_tiles = (g.M + 16 * MT - 1) / (16 * MT), n_tiles = g.N / (64 * NF);
-  const dim3 grid(8 * ((n_tiles + 7) / 8) * m_tiles);
-  if (!g.a_lo) {
-    whole_k_kernel<MT, NF, GEMM_STORE_F32, false><<<grid, 768, 0, s>>>(g);
-    return hipGetLastError();
-  }
-  switch (g.epilogue) {
-    case GEMM_STORE_F32: whole_k_kernel<MT, NF, GEMM_STORE_F32, true><<<grid, 768, 0, s>>>(g); break;
-    case GEMM_ADD_F32: whole_k_kernel<MT, NF, GEMM_ADD_F32, true><<<grid, 768, 0, s>>>(g); break;
-    case GEMM_SWIGLU: whole_k_kernel<MT, NF, GEMM_SWIGLU, true><<<grid, 768, 0, s>>>(g); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
 hipError_t launch_proj_k64_whole(int mt, int nf, GemmArgs g, hipStream_t s) {
   // At the same k all blocks ask the same memory channels; starting at different ones spreads them, but every XCD then reads all
-  // activations at any time: up to 3 MB of them stay in its 4 MB of L2.  The rows after it are then sums from another k on, which only
-  // the high part alone (LM heads) may be: their logits move by 4e-6 of the norm, while the K and V rows behind a gate/up projection
-  // that started elsewhere round to bf16 the other way (1e-4 of the norm in the 8B shape, 4e-4 in the 70B).  LM head at 32 / 64 / 128
-  // rows, 8B 59.8 / 62.9 / 63.8 -> 43.3 / 44.7 / 53.0 us, 70B 114 / 116 / 127 -> 85 / 88 / 102.
-  g.rotate = !g.a_lo && g.M <= 16 * mt && (size_t)g.M * g.K * 2 <= ((size_t)3 << 20) && g.K >= 2048;
-  if (nf == 2) {
-    switch (mt) {
-      case 1: return launch_whole<1, 2>(g, s);
-      case 2: return launch_whole<2, 2>(g, s);
-      case 3: return launch_whole<3, 2>(g, s);
-      case 4: return launch_whole<4, 2>(g, s);
-      case 5: return launch_whole<5, 2>(g, s);
-      case 6: return launch_whole<6, 2>(g, s);
-      case 7: return launch_whole<7, 2>(g, s);
-      case 8: return launch_whole<8, 2>(g, s);
-      case 9: return launch_whole<9, 2>(g, s);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  if (nf == 4) {
-    switch (mt) {
-      case 1: return launch_whole<1, 4>(g, s);
-      case 2: return launch_whole<2, 4>(g, s);
-      case 3: return launch_whole<3, 4>(g, s);
-      case 4: return launch_whole<4, 4>(g, s);
-      case 5: return launch_whole<5, 4>(g, s);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  return hipErrorInvalidValue;
+  // activations at any time: up to 3 MB of them stay in its 4 MB of L2.  LM head at 32 / 64 / 128 rows, 8B 59.8 / 62.9 / 63.8 ->
+  // 43.3 / 44.7 / 53.0 us, 70B 114 / 116 / 127 -> 85 / 88 / 102.
+  g.rotate = g.M <= 16 * mt && (size_t)g.M * g.K * 2 <= ((size_t)3 << 20) && g.K >= 2048;
+  return with_short_tile(mt, nf, [&](auto MT, auto NF) {
+    constexpr int mt_ = decltype(MT)::value, nf_ = decltype(NF)::value;
+    const int m_tiles = (g.M + 16 * mt_ - 1) / (16 * mt_), n_tiles = g.N / (64 * nf_);
+    whole_k_kernel<mt_, nf_><<<8 * ((n_tiles + 7) / 8) * m_tiles, 768, 0, s>>>(g);
+    return hipGetLastError();
+  });
 }

@@ -494,6 +494,33 @@ def test_gemm_short_tiles_whole_and_sliced(tile, M, N, K):
     assert (high.double() - a.double() @ w.double().T).abs().max().item() < tol
 
 
+@pytest.mark.parametrize("K", [1024, 4160])
+@pytest.mark.parametrize("tile", list(range(201, 206)) + list(range(301, 310)))
+def test_gemm_whole_k_has_the_bits_of_the_tile_with_one_step_per_stage(tile, K):
+    """One tile of rows, K whole, 16 and 65 stages: the same products added in the same order (k ascending, high part before low)
+    whichever kernel takes them, for every epilogue."""
+    synera = _synera()
+    M, N = 16 * (tile % 100) - 3, 512
+    g = torch.Generator(device=DEV).manual_seed(13 * tile + K)
+    a, al = synera.split_pair(torch.randn((M, K), generator=g, device=DEV))
+    w = wl.draw_normal_bf16((N, K), 0.02, 43, DEV)
+    base = torch.randn((M, N), generator=g, device=DEV)
+    halves = w[: N // 2].contiguous(), w[N // 2:].contiguous()
+    got = []
+    try:
+        for t in (tile, tile - 200):
+            synera.debug_set_gemm_tile(t)
+            added, act = base.clone(), [torch.zeros((M, N // 2), dtype=torch.float16, device=DEV) for _ in range(2)]
+            synera.debug_gemm_epilogue(a, al, w, None, added, None, 1)
+            synera.debug_gemm_epilogue(a, al, *halves, *act, 2)
+            got.append([synera.gemm_pair(a, al, w), added, *act])
+            torch.cuda.synchronize()
+    finally:
+        synera.debug_set_gemm_tile(-1)
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("tile", [302, 303, 308, 202, 203, 205])
 def test_gemm_slices_have_the_bits_of_the_tile_with_one_step_per_stage(tile):
     """Eight slices of 2048: each sums its k in order, whatever the stage, the column tile or the way the weights are read."""
