@@ -132,6 +132,26 @@ def test_config4_70b_shape_cut_to_8_layers_with_a_draft_chain():
     assert kv["ok"], kv["fail"]
 
 
+def test_70b_shape_cut_to_8_layers_over_short_contexts():
+    """The wide shape where its sums are cut most finely (81 to 144 rows: QKV in 6 slices, output and down in 8) and what a chunk
+    appends carries most of the attention: 13 requests over 24 to 60 keys, 122 rows, against the float64 oracle, at the bars of every
+    configuration (measured: logits 7.7e-3, where the oracle's own float32 run lands 9.5e-3 away; 9 % of the appended entries round
+    the other way)."""
+    import dataclasses
+    rec = wl.config(4)
+    rec = dataclasses.replace(rec, shape=dataclasses.replace(rec.shape, n_layers=8), batch=13, ctx_lo=24, ctx_hi=60, k_hi=9)
+    b = wl.draw_batch(rec)
+    rows = int(b["n_draft"].sum()) + len(b["n_draft"])
+    assert 113 <= rows <= 144
+    for n, k, epi, slices in ((10240, 8192, 0, 6), (8192, 28672, 1, 8)):
+        assert synera.debug_gemm_plan(rows, n, k, epi)[2] == slices
+    weights = gh.draw_weights(rec.shape, rec.seed, DEV, lazy_oracle=True)
+    rep, kv = gh.one_pass_parity(rec, weights, DEV, tag="70B shape, 8 layers, short contexts")
+    assert rep["requests_checked"] == 13
+    assert rep["ok"], rep["fail"]
+    assert kv["ok"], kv["fail"]
+
+
 def test_config4_70b_all_80_layers():
     """Config 4 at its full depth (140 GB of weights on the GPU).  The oracle widens one layer at a time from the
     device copy, so it can afford one pass over the 80 layers, not the nine of a greedy draft chain: the one-pass
