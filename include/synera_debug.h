@@ -109,6 +109,13 @@ int32_t synera_measure_mfma_f16(float* d_out, int32_t blocks, int32_t iters, int
 int32_t synera_debug_set_gemm_tile(int32_t tile);
 
 /*
+ * Test hook: 1 / 0 has every later tile with 64-wide stages read its weights as not wanted again / as ordinary ones, -1
+ * restores the automatic choice (weights that no cache holds until the next call are not wanted again).  The
+ * result has the same bits either way.  Process-wide.
+ */
+int32_t synera_debug_set_gemm_once(int32_t once);
+
+/*
  * Test hook, host only (no GPU call, no context): the work plan of the chunk attention of Section 3.2 for one
  * batch, as synera_verify lays it out for `attn_blocks` (2 .. 8192) persistent blocks.  Inputs as for
  * synera_verify (host).

@@ -87,6 +87,8 @@ _lib.synera_debug_read_scratch.restype = C.c_int32
 _lib.synera_debug_read_scratch.argtypes = [_vp, C.c_int32, _vp, C.c_int64, _vp]
 _lib.synera_debug_set_gemm_tile.restype = C.c_int32
 _lib.synera_debug_set_gemm_tile.argtypes = [C.c_int32]
+_lib.synera_debug_set_gemm_once.restype = C.c_int32
+_lib.synera_debug_set_gemm_once.argtypes = [C.c_int32]
 _lib.synera_stochastic_accept.restype = C.c_int32
 _lib.synera_stochastic_accept.argtypes = [_vp, _vp, C.c_int32, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
 _lib.synera_topp_count.restype = C.c_int32
@@ -400,6 +402,11 @@ def debug_gemm_plan_bk(M, N, K, epilogue=0, stored_slices=True):
 def debug_set_gemm_tile(variant):
     """Tuning hook: force a GEMM tile configuration (-1 = automatic)."""
     _lib.synera_debug_set_gemm_tile(variant)
+
+
+def debug_set_gemm_once(once):
+    """Test hook: read weights as not wanted again (1) or as ordinary ones (0); -1 = automatic.  The same bits."""
+    _lib.synera_debug_set_gemm_once(once)
 
 
 class Verifier:

@@ -234,9 +234,9 @@ extern "C" int32_t synera_create(synera_ctx** out, const synera_model_desc* desc
   uintptr_t gains = reinterpret_cast<uintptr_t>(w->final_norm);
   for (const synera_layer_weights& lw : c->layers) gains |= reinterpret_cast<uintptr_t>(lw.attn_norm) | reinterpret_cast<uintptr_t>(lw.mlp_norm);
   c->streams = m.d_ffn % 128 == 0 && m.d_model <= SY_STREAM_NORM_WIDTH && (gains & 15) == 0;
-  // 256 MB: the last-level cache.  (A decoder of 7 MB whose weights were marked all the same took 89.7 instead of 88.1 us a verify.)
+  // (A decoder of 7 MB whose weights were marked all the same took 89.7 instead of 88.1 us a verify.)
   const size_t per_layer = (size_t)m.d_model * (2 * m.n_q_heads * m.head_dim + 2 * m.n_kv_heads * m.head_dim) + 3 * (size_t)m.d_model * m.d_ffn;
-  c->weights_once = 2 * (m.n_layers * per_layer + (size_t)m.vocab * m.d_model) > ((size_t)256 << 20);
+  c->weights_once = beyond_caches(2 * (m.n_layers * per_layer + (size_t)m.vocab * m.d_model));
   c->max_batch = max_batch;
   c->max_tokens = max_tokens;
   c->max_pages = max_pages;
@@ -740,7 +740,7 @@ static int32_t verify_launches(synera_ctx* c, const Plan& p, int32_t B, const in
   al.hd = hd;
   // No cache holds the keys until the next verify (see weights_once), and most of them are read by one block: where chunks of
   // 18 tokens (72 rows: two groups) made every stream two, a layer took 8 us longer with its keys marked.
-  al.once = (c->weights_once || (size_t)p.total_keys * m.n_layers * kd * 4 > ((size_t)256 << 20)) && 2 * p.keys_shared < p.total_keys;
+  al.once = (c->weights_once || beyond_caches((size_t)p.total_keys * m.n_layers * kd * 4)) && 2 * p.keys_shared < p.total_keys;
 
   // Which projections read their activation pair as one paired array (the producer writes it that way then).  The
   // ablation of low parts works on separate arrays: any of its bits keeps them.
@@ -1142,6 +1142,11 @@ extern "C" int32_t synera_debug_set_gemm_tile(int32_t variant) {
   return SYNERA_OK;
 }
 
+extern "C" int32_t synera_debug_set_gemm_once(int32_t once) {
+  gemm_force_once(once);
+  return SYNERA_OK;
+}
+
 extern "C" int32_t synera_debug_attention_plan(const synera_model_desc* desc, int32_t attn_blocks, int32_t B,
                                                const int32_t* h_ctx_len, const int32_t* h_n_uncached,
                                                const int32_t* h_n_draft, const int32_t* h_block_table,
@@ -1228,6 +1233,10 @@ extern "C" int32_t synera_debug_gemm_plan_bk(int32_t M, int32_t N, int32_t K, in
   return SYNERA_OK;
 }
 
+// A projection on its own: what another call of it finds in the caches is these weights.  Marked as not wanted again all the
+// same, 28672 x 4096 (235 MB) at 32 rows took 50.5 instead of 35.7 us a call; 32000 x 8192 (524 MB) 91.8 instead of 109.9.
+static bool alone_once(int32_t N, int32_t K) { return beyond_caches((size_t)2 * N * K); }
+
 extern "C" int32_t synera_debug_gemm_epilogue(const void* d_a, const void* d_a_lo, const void* d_w0, const void* d_w1,
                                               void* d_c, void* d_c_lo, int32_t M, int32_t N, int32_t K,
                                               int32_t epilogue, void* stream) {
@@ -1237,7 +1246,7 @@ extern "C" int32_t synera_debug_gemm_epilogue(const void* d_a, const void* d_a_l
   const bool glu = epilogue == GEMM_SWIGLU;
   return run_gemm(static_cast<const uint16_t*>(d_a), static_cast<const uint16_t*>(d_a_lo), 1.0f, d_w0, glu ? N / 2 : N,
                   glu ? d_w1 : nullptr, glu ? N / 2 : 0, nullptr, 0, d_c, d_c_lo, M, N, K, epilogue,
-                  static_cast<hipStream_t>(stream), true);
+                  static_cast<hipStream_t>(stream), alone_once(N, K));
 }
 
 extern "C" int32_t synera_debug_gemm_paired(const void* d_a_pairs, const void* d_w0, const void* d_w1, void* d_c,
@@ -1247,7 +1256,7 @@ extern "C" int32_t synera_debug_gemm_paired(const void* d_a_pairs, const void* d
   if (N % (epilogue == GEMM_SWIGLU ? 256 : 128) != 0 || K % 64 != 0) return SYNERA_EUNSUP;
   const bool glu = epilogue == GEMM_SWIGLU;
   return run_gemm(static_cast<const uint16_t*>(d_a_pairs), nullptr, 1.0f, d_w0, glu ? N / 2 : N, glu ? d_w1 : nullptr,
-                  glu ? N / 2 : 0, nullptr, 0, d_c, nullptr, M, N, K, epilogue, static_cast<hipStream_t>(stream), true,
+                  glu ? N / 2 : 0, nullptr, 0, d_c, nullptr, M, N, K, epilogue, static_cast<hipStream_t>(stream), alone_once(N, K),
                   nullptr, nullptr, true, glu);
 }
 
@@ -1259,7 +1268,7 @@ extern "C" int32_t synera_debug_gemm_slices(const void* d_a, const void* d_a_lo,
   int n_parts = 0;
   const int32_t st = run_gemm(static_cast<const uint16_t*>(d_a), static_cast<const uint16_t*>(d_a_lo), 1.0f, d_w, N,
                               nullptr, 0, nullptr, 0, d_parts, nullptr, M, N, K, GEMM_STORE_F32,
-                              static_cast<hipStream_t>(stream), true, d_parts, &n_parts);
+                              static_cast<hipStream_t>(stream), alone_once(N, K), d_parts, &n_parts);
   *h_n_parts = n_parts > 0 ? n_parts : 1;
   return st;
 }
@@ -1269,7 +1278,7 @@ extern "C" int32_t synera_gemm_pair(const void* d_a, const void* d_a_lo, const v
   if (!d_a || !d_w || !d_c || M < 1 || N < 1 || K < 1) return SYNERA_EINVAL;
   if (N % 128 != 0 || K % 64 != 0) return SYNERA_EUNSUP;
   return run_gemm(static_cast<const uint16_t*>(d_a), static_cast<const uint16_t*>(d_a_lo), 1.0f, d_w, N, nullptr, 0,
-                  nullptr, 0, d_c, nullptr, M, N, K, GEMM_STORE_F32, static_cast<hipStream_t>(stream), true);
+                  nullptr, 0, d_c, nullptr, M, N, K, GEMM_STORE_F32, static_cast<hipStream_t>(stream), alone_once(N, K));
 }
 
 extern "C" int32_t synera_debug_set_lo_off(synera_ctx* c, int32_t sites) {

@@ -191,6 +191,9 @@ hipError_t launch_importance_dispatch(const float* importance, const int32_t* cu
 
 // ---------------------------------------------------------------- gemm.hip
 enum GemmEpilogue { GEMM_STORE_F32 = 0, GEMM_ADD_F32 = 1, GEMM_SWIGLU = 2 };
+// Whether this many bytes, read once per call, are no longer in the last-level cache (256 MB) when the next call wants them.
+inline bool beyond_caches(size_t bytes) { return bytes > ((size_t)256 << 20); }
+
 struct GemmArgs {
   const uint16_t* a;     // [M][K], high part of the activation's fp16 pair -- or, with a_paired, the whole pair as
                          // [M][K / 32][hi 32 | lo 32] (a_lo unused)
@@ -218,6 +221,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 int gemm_pick_split(const GemmArgs& g);                             // K slices launch_gemm should be given (1 without c_parts)
 void gemm_plan(const GemmArgs& g, int* bm, int* bn, int* split);    // tile and K slices launch_gemm would use (host only)
 void gemm_force_variant(int v);   // tuning hook: -1 automatic, else tile rows / 16 + (128-column tile ? 100 : 0) + (BK = 64 ? 200 : 0)
+void gemm_force_once(int v);      // test hook: forces GemmArgs::once, -1 leaves it
 int gemm_plan_bk(const GemmArgs& g);                               // K extent of a stage the plan uses (32 or 64)
 // the instantiations live in three translation units (compile time)
 hipError_t launch_proj_nf4_low(int mt, const GemmArgs& g, hipStream_t s);    // 256 columns, 16 .. 144 rows

@@ -10,6 +10,8 @@
 
 static int g_forced = -1;   // tuning hook: forced tile (see gemm_force_variant), -1 = automatic
 void gemm_force_variant(int v) { g_forced = v; }
+static int g_forced_once = -1;   // test hook: forced GemmArgs::once, -1 = the caller's
+void gemm_force_once(int v) { g_forced_once = v; }
 
 static bool tile_fits(const GemmArgs& g, int mt, int nf, int ksub) {
   if (mt < 1 || (nf == 4 ? mt > 17 : mt > 12)) return false;
@@ -159,7 +161,11 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     }
     if (rows != g.N) return hipErrorInvalidValue;
   }
-  if (ksub == 2) return launch_proj_k64(mt, nf, g, s);
+  if (ksub == 2) {
+    GemmArgs a = g;
+    if (g_forced_once >= 0) a.once = g_forced_once != 0;
+    return launch_proj_k64(mt, nf, a, s);
+  }
   if (nf == 2) return launch_proj_nf2(mt, g, s);
   return mt <= 9 ? launch_proj_nf4_low(mt, g, s) : launch_proj_nf4_high(mt, g, s);
 }

@@ -64,6 +64,7 @@ extern "C" int32_t synera_gemm_pair_static(const void* d_a, const void* d_a_lo, 
   g.epilogue = GEMM_STORE_F32;
   g.split_k = 1;
   g.c_parts = parts;
+  g.once = beyond_caches((size_t)2 * N * K);
   g.out_scale = 1.0f / (float)(1 << SY_W_SHIFT);
   g.c_scale = 1.0f;
   g.split_k = gemm_pick_split(g);               // <= SYNERA_MAX_GEMM_SLICES

@@ -498,7 +498,8 @@ def test_gemm_short_tiles_whole_and_sliced(tile, M, N, K):
 @pytest.mark.parametrize("tile", list(range(201, 206)) + list(range(301, 310)))
 def test_gemm_whole_k_has_the_bits_of_the_tile_with_one_step_per_stage(tile, K):
     """One tile of rows, K whole, 16 and 65 stages: the same products added in the same order (k ascending, high part before low)
-    whichever kernel takes them, for every epilogue."""
+    whichever kernel takes them and however it reads the weights, for every epilogue.  The high part alone (LM heads) has an order of
+    its own, the same for both ways to read."""
     synera = _synera()
     M, N = 16 * (tile % 100) - 3, 512
     g = torch.Generator(device=DEV).manual_seed(13 * tile + K)
@@ -506,10 +507,12 @@ def test_gemm_whole_k_has_the_bits_of_the_tile_with_one_step_per_stage(tile, K):
     w = wl.draw_normal_bf16((N, K), 0.02, 43, DEV)
     base = torch.randn((M, N), generator=g, device=DEV)
     halves = w[: N // 2].contiguous(), w[N // 2:].contiguous()
-    got = []
+    got, high = [], []
     try:
-        for t in (tile, tile - 200):
+        for t, once in ((tile - 200, -1), (tile, 0), (tile, 1)):
             synera.debug_set_gemm_tile(t)
+            synera.debug_set_gemm_once(once)
+            high.append(synera.gemm_pair(a, None, w))
             added, act = base.clone(), [torch.zeros((M, N // 2), dtype=torch.float16, device=DEV) for _ in range(2)]
             synera.debug_gemm_epilogue(a, al, w, None, added, None, 1)
             synera.debug_gemm_epilogue(a, al, *halves, *act, 2)
@@ -517,8 +520,11 @@ def test_gemm_whole_k_has_the_bits_of_the_tile_with_one_step_per_stage(tile, K):
             torch.cuda.synchronize()
     finally:
         synera.debug_set_gemm_tile(-1)
-    for x, y in zip(*got):
-        assert torch.equal(x, y)
+        synera.debug_set_gemm_once(-1)
+    for x, y, z in zip(*got):
+        assert torch.equal(x, y) and torch.equal(x, z)
+    assert torch.equal(high[1], high[2])
+    assert (high[1].double() - a.double() @ w.double().T).abs().max().item() < 6e-9 * K + 2e-7
 
 
 @pytest.mark.parametrize("tile", [302, 303, 308, 202, 203, 205])
@@ -531,13 +537,15 @@ def test_gemm_slices_have_the_bits_of_the_tile_with_one_step_per_stage(tile):
     w = wl.draw_normal_bf16((N, K), 0.02, 41, DEV)
     got = []
     try:
-        for t in (tile, tile - 200):
+        for t, once in ((tile - 200, -1), (tile, 0), (tile, 1)):
             synera.debug_set_gemm_tile(t)
+            synera.debug_set_gemm_once(once)
             got.append(synera.debug_gemm_slices(a, al, w).clone())
             torch.cuda.synchronize()
     finally:
         synera.debug_set_gemm_tile(-1)
-    assert got[0].shape[0] == 8 and torch.equal(got[0], got[1])
+        synera.debug_set_gemm_once(-1)
+    assert got[0].shape[0] == 8 and torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
 
 
 def test_gemm_rejects_unsupported_shapes():
