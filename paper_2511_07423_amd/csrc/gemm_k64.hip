@@ -2,7 +2,8 @@
 //   * the high part alone, K at least 16 stages long (LM heads): gemm_k64_whole.hip;
 //   * pairs, weights that no cache holds: gemm_k64_once.hip.  Gate/up of the 8B shape at 32 / 64 / 128 rows 50.8 / 56.0 / 70.0 ->
 //     49.2 / 54.2 / 66.2 us, of the 70B 203 / 202 / 308 -> 180 / 184 / 255 (above 80 rows on 128 instead of 256 columns); down projection
-//     of the 8B at 128 rows 37.1 -> 35.9;
+//     of the 8B at 128 rows 37.1 -> 35.9.  Several tiles of rows, which want the same lines out of one XCD's L2, gain as well: 4096 x
+//     4096 in slices at 224 / 560 rows 24.9 / 45.4 -> 23.2 / 43.3, 2048 x 2048 at 192 / 256 11.5 / 12.6 -> 11.2 / 11.9;
 //   * the rest, here.
 // Pairs are summed in the order of the tiles with one K step per stage, so a product has one set of bits whatever the tile.  The
 // kernel for LM heads, which adds two halves of every stage's K at the end, took 49.2 / 54.5 / 66.2 us for gate/up where it kept to

@@ -210,6 +210,9 @@ hipError_t launch_proj_k64_whole(int mt, int nf, GemmArgs g, hipStream_t s) {
   // activations at any time: up to 3 MB of them stay in its 4 MB of L2.  LM head at 32 / 64 / 128 rows, 8B 59.8 / 62.9 / 63.8 ->
   // 43.3 / 44.7 / 53.0 us, 70B 114 / 116 / 127 -> 85 / 88 / 102.
   g.rotate = g.M <= 16 * mt && (size_t)g.M * g.K * 2 <= ((size_t)3 << 20) && g.K >= 2048;
+  // Several tiles of rows want the same weight lines out of one XCD's L2: 200 rows with lines marked as not wanted again 8B 97.1 -> 101.8
+  // us, 70B 184.9 -> 192.8; 224 to 280 rows the same within 1 %.
+  g.once = g.once && g.M <= 16 * mt;
   return with_short_tile(mt, nf, [&](auto MT, auto NF) {
     constexpr int mt_ = decltype(MT)::value, nf_ = decltype(NF)::value;
     const int m_tiles = (g.M + 16 * mt_ - 1) / (16 * mt_), n_tiles = g.N / (64 * nf_);
