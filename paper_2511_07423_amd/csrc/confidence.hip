@@ -254,25 +254,10 @@ __global__ __launch_bounds__(TOPK_THREADS) void confidence_topk_kernel(const voi
         if (c < rd.n_vec) take(raw, c, gmax[j]);
       }
     }
-  } else if constexpr (BF16 && NV == 16) {             // four loads at a time (asked for ahead, four registers more: 700 x 50257 25.9 -> 26.7 us)
-    constexpr int FLY = 4;                           // loads in flight per thread
-#pragma unroll
-    for (int j0 = 0; j0 < NV; j0 += FLY) {
-      uint4 raw[FLY];
-#pragma unroll
-      for (int f = 0; f < FLY; ++f) {
-        const int c = (j0 + f) * TOPK_THREADS + tid;
-        raw[f] = c < rd.n_vec ? rd.raw(c) : make_uint4(0u, 0u, 0u, 0u);
-      }
-#pragma unroll
-      for (int f = 0; f < FLY; ++f) {
-        const int c = (j0 + f) * TOPK_THREADS + tid;
-        if (c < rd.n_vec) take(raw[f], c, gmax[j0 + f]);
-      }
-    }
   } else if (rd.n_vec > 0) {
     // four loads always in flight per thread (four at a time, of which the fifth waited for the fourth's arithmetic: 2000 x 32000 f32,
-    // k = 160, 56.3 -> 53.8 us, 2048 x 128256 bf16 115 -> 110)
+    // k = 160, 56.3 -> 53.8 us, 2048 x 128256 bf16 115 -> 110; bf16 rows of 33000 to 65000 entries, k = 160, 256 rows 20.3 -> 19.2, 1024
+    // rows 47.6 -> 42.0 at 65000, 33.6 -> 33.3 at 33000; but 700 rows 32.7 -> 33.4 and 25.0 -> 25.5)
     constexpr int FLY = 4;
     const int last = rd.n_vec - 1;
     uint4 raw[FLY];
@@ -1165,7 +1150,9 @@ hipError_t launch_confidence(const void* logits, int dtype, int64_t rows, int64_
   if (rows <= 0) return hipSuccess;
   // Matrices that no cache holds are read as not wanted again (nt).  2048 x 128256 bf16 (525 MB): 99.6 -> 89.8 us; 1131 x
   // 32000 f32 (145 MB, just written by the LM head): 28.7 -> 27 us; below, what a cache still holds counts: 589 x 32000 (75 MB)
-  // 14.8 -> 15.1, 5 rows 9.6 -> 10.9 us.
+  // 14.8 -> 15.1, 5 rows 9.6 -> 10.9 us.  Rows that do not start on a 128-byte line, and so share lines, gain as well: bf16 2048 x 50257
+  // (pitch 50264) 42.2 -> 40.6, 2048 x 100277 78.7 -> 74.8, f32 1024 x 50257 38.0 -> 34.6; about 1000 rows of bf16 lose 1 to 2 %
+  // (1024 x 128256 50.1 -> 51.0, 900 x 100001 38.8 -> 39.2).
   const bool once = rows * vocab * (dtype == 1 ? 2 : 4) > (128 << 20);
   auto* kernel = dtype == 1 ? (once ? confidence_kernel<true, true> : confidence_kernel<true, false>)
                             : (once ? confidence_kernel<false, true> : confidence_kernel<false, false>);
