@@ -38,9 +38,11 @@ static bool may_slice(const GemmArgs& g) { return g.epilogue != GEMM_SWIGLU && g
 // compute unit pulls from HBM.  This fit stays as it is: see may_slice.
 // Whole K: tiles with one K step per stage ask for weights by half lines, and short ones wait for that: 70B gate/up projection as one
 // tile of 96, 128, 160, 208 rows 1.0, 1.12, 1.19, 1.35 us (0.65 + 0.055 per row block), LM heads of the high part alone 0.85
-// at any height.  Two K steps per stage: 8B gate/up at 32 .. 144 rows 0.69 .. 1.02 us, 256 columns (70B) at 32 .. 80 rows 1.37 .. 1.45,
-// the 70B's 96 .. 144 rows on 128 columns (two rounds of blocks) 0.87 .. 1.06; LM heads (gemm_k64_whole.hip) 1.13x with several
-// rounds of blocks, or several tiles of rows to read the same weights.
+// at any height, 0.75 in several rounds (two of their blocks share a compute unit; with 0.85 for those too, 545 to 576 rows took 192 x
+// 128 instead of 144 x 256: 8B 199 instead of 191 us, 70B 370 instead of 362).  Two K steps per stage: 8B gate/up at 32 .. 144
+// rows 0.69 .. 1.02 us, 256 columns (70B) at 32 .. 80 rows 1.37 .. 1.45, the 70B's 96 .. 144 rows on 128 columns (two rounds of
+// blocks) 0.87 .. 1.06; LM heads (gemm_k64_whole.hip) 1.13x with several rounds of blocks, or several tiles of rows to read the
+// same weights.
 static double step_us(const GemmArgs& g, int mt, int nf, int ksub, bool one_tile, bool one_round) {
   const bool lo = g.a_lo != nullptr || g.a_paired;
   if (!may_slice(g) && ksub == 2 && g.K >= 1024) {
@@ -51,7 +53,7 @@ static double step_us(const GemmArgs& g, int mt, int nf, int ksub, bool one_tile
   double stream = ksub * 64 * nf * 64 / 24e3;
   if (!may_slice(g) && ksub == 1) {
     if (one_tile) stream = nf / 4.0 * (0.65 + 0.055 * mt);
-    if (!lo) stream = std::max(stream, nf / 4.0 * 0.85);
+    if (!lo) stream = std::max(stream, nf == 2 ? 0.425 : one_round ? 0.85 : 0.75);
   }
   return std::max(mfma, stream);
 }
